@@ -35,6 +35,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <memory>
 #include <string>
 #include <type_traits>
@@ -673,76 +674,20 @@ sl_status upload_image(sl_packed_weight *w)
                 om[((size_t)wi * ncg + g) * 2 + 1] = pp[0];
             }
     }
-    // weight panels, one table per tile-group size of the weight-stationary shapes
-    std::vector<int> pnts;
-    for (const PanelCfg &c : kPanelCfgs)
-        if (std::find(pnts.begin(), pnts.end(), c.nt) == pnts.end()) pnts.push_back(c.nt);
-    if ((int)pnts.size() > kMaxPanTables) {
-        set_error("internal: too many weight-panel sizes");
+    // the dense operand image, from the canonical blocks
+    const uint64_t dense_bytes = (uint64_t)ti.n_win * ti.n_tiles * kDenseOp;
+    if (dense_bytes > (uint64_t)kMaxBufferBytes) {
+        set_error("packed weight image over 2 GiB (n_out x k_in too large for one image)");
         return SL_ERR_UNSUPPORTED;
     }
-    std::vector<std::vector<uint32_t>> pans(pnts.size());
-    std::vector<uint32_t> pan_max(pnts.size(), 0);
-    for (size_t i = 0; i < pnts.size(); ++i) {
-        const int nt = pnts[i];
-        const int ncg = (ti.n_tiles + nt - 1) / nt;
-        std::vector<uint32_t> &pt = pans[i];
-        pt.assign((size_t)ncg * (ti.n_win + 1) * 4, 0u);
-        for (int g = 0; g < ncg; ++g) {
-            const int t0 = g * nt, ntl = std::min(nt, ti.n_tiles - t0);
-            uint64_t base = 0;
-            for (int wi = 0; wi < ti.n_win; ++wi) {
-                const uint32_t *pp = ti.ovf_ptr.data() + (size_t)wi * pstride + t0;
-                uint32_t mask = 0;
-                for (int j = 0; j < ntl; ++j) mask |= (pp[j + 1] > pp[j] ? 1u : 0u) << j;
-                uint32_t *e = &pt[((size_t)g * (ti.n_win + 1) + wi) * 4];
-                e[0] = mask;
-                e[1] = pp[0];
-                e[2] = (uint32_t)std::min<uint64_t>(base, UINT32_MAX);
-                base += (uint64_t)(2 * nt) * kOpPieces;
-            }
-            pt[((size_t)g * (ti.n_win + 1) + ti.n_win) * 4 + 2] = (uint32_t)std::min<uint64_t>(base, UINT32_MAX);
-            pan_max[i] = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(pan_max[i], base), UINT32_MAX);
+    std::vector<int8_t> dense((size_t)dense_bytes, 0);
+    for (int32_t g = 0; g < w->n_out / 4; ++g)
+        for (uint32_t e = w->row_ptr[g]; e < w->row_ptr[g + 1]; ++e) {
+            const int32_t c = w->col[e] % kWin;
+            int8_t *const op = dense.data() + ((size_t)(w->col[e] / kWin) * ti.n_tiles + g / 4) * kDenseOp +
+                               (c % 32 / 16) * 1024 + (16 * (c / 32) + 4 * (g % 4)) * 16 + c % 16;
+            for (int r = 0; r < 4; ++r) op[16 * r] = w->vals[4 * (size_t)e + r];
         }
-    }
-    // The panel images: per channel group, its window table and then its
-    // panel (per window: the NT main operands, zeros past the last tile, then
-    // NT overflow operand slots, zeros where a tile has none), padded to a
-    // common stride of whole 1024-byte copies, so that a workgroup's copies
-    // need no table read first and its kernel none at all.
-    // Only sizes whose panels can fit in LDS get an image.
-    std::vector<std::vector<int8_t>> pimgs(pnts.size());
-    std::vector<uint32_t> pstrides(pnts.size(), 0);
-    for (size_t i = 0; i < pnts.size(); ++i) {
-        const int nt = pnts[i];
-        const int ncg = (ti.n_tiles + nt - 1) / nt;
-        const uint64_t tab = (uint64_t)(ti.n_win + 1) * 16;
-        const uint64_t stride = (tab + (uint64_t)pan_max[i] * 16 + 1023) / 1024 * 1024;
-        if (stride > kLdsMax || (uint64_t)ncg * stride > (uint64_t)kMaxBufferBytes) continue;
-        pstrides[i] = (uint32_t)stride;
-        std::vector<int8_t> &im = pimgs[i];
-        im.assign((size_t)ncg * stride, 0);
-        const std::vector<uint32_t> &pt = pans[i];
-        for (int g = 0; g < ncg; ++g) {
-            int8_t *const gb = im.data() + (size_t)g * stride;
-            const uint32_t *const ge = pt.data() + (size_t)g * (ti.n_win + 1) * 4;
-            memcpy(gb, ge, (size_t)tab);
-            const int t0 = g * nt, ntl = std::min(nt, ti.n_tiles - t0);
-            for (int wi = 0; wi < ti.n_win; ++wi) {
-                int8_t *const wb = gb + tab + (size_t)ge[wi * 4 + 2] * 16;
-                memcpy(wb, ti.main.data() + ((size_t)wi * ti.n_tiles + t0) * kOpBytes, (size_t)ntl * kOpBytes);
-                // (the window's overflow operands are stored in tile order
-                // from entry word 1 on)
-                uint32_t rank = 0;
-                for (int j = 0; j < ntl; ++j)
-                    if ((ge[wi * 4] >> j) & 1u) {
-                        memcpy(wb + (size_t)(nt + j) * kOpBytes,
-                               ti.ovf.data() + (size_t)(ge[wi * 4 + 1] + rank) * kOpBytes, kOpBytes);
-                        ++rank;
-                    }
-            }
-        }
-    }
     // the dense overflow image of the split-reduction and direct kernels: a
     // tile's overflow operand of a window at the offset of its main operand,
     // zeros where it has none (the same size as the main image, which is
@@ -771,11 +716,8 @@ sl_status upload_image(sl_packed_weight *w)
         o_om[i] = o_end;
         o_end = align256(o_end + oms[i].size() * sizeof(uint32_t));
     }
-    std::vector<size_t> o_pan(pnts.size());
-    for (size_t i = 0; i < pnts.size(); ++i) {
-        o_pan[i] = o_end;
-        o_end = align256(o_end + pimgs[i].size());
-    }
+    const size_t o_dense = o_end;
+    o_end = align256(o_end + dense.size());
     const size_t o_ovfd = o_end;
     o_end = align256(o_end + b_main);
     const size_t total = o_end;
@@ -799,15 +741,9 @@ sl_status upload_image(sl_packed_weight *w)
         w->dev.om[i] = reinterpret_cast<const uint32_t *>(p + o_om[i]);
     }
     w->dev.n_om = (int32_t)nts.size();
-    for (size_t i = 0; i < pnts.size(); ++i) {
-        if (!pimgs[i].empty())
-            HIP_TRY(hipMemcpy(p + o_pan[i], pimgs[i].data(), pimgs[i].size(), hipMemcpyHostToDevice));
-        w->dev.pan_nt[i] = pnts[i];
-        w->dev.pan_pieces[i] = (int32_t)std::min<uint32_t>(pan_max[i], INT32_MAX);
-        w->dev.pan_stride[i] = pstrides[i];
-        w->dev.pan[i] = pimgs[i].empty() ? nullptr : reinterpret_cast<const int8_t *>(p + o_pan[i]);
-    }
-    w->dev.n_pan = (int32_t)pnts.size();
+    HIP_TRY(hipMemcpy(p + o_dense, dense.data(), dense.size(), hipMemcpyHostToDevice));
+    w->dev.dense = reinterpret_cast<const int8_t *>(p + o_dense);
+    w->dev.dense_bytes = (uint32_t)dense.size();
     if (!odense.empty()) HIP_TRY(hipMemcpy(p + o_ovfd, odense.data(), odense.size(), hipMemcpyHostToDevice));
     w->dev.ovfd = reinterpret_cast<const int8_t *>(p + o_ovfd);
     w->dev.ovfd_bytes = (uint32_t)odense.size();
@@ -1008,36 +944,55 @@ static bool one_full_round(bool direct, int64_t m, const sl_packed_weight *w)
     return items <= n_cu && items * 5 >= (int64_t)n_cu * 4;
 }
 
+// Token slices of a weight-stationary launch: `want` per channel group.
+static void set_panel_slices(LinearArgs &a, PanelCfg c, int64_t n_cg, int64_t want)
+{
+    const int64_t groups = ((a.m + 15) / 16 * 16 + c.tg() - 1) / c.tg();
+    const int64_t sg = std::max<int64_t>(1, (groups + want - 1) / want);
+    a.n_cgroups = (int32_t)n_cg;
+    a.slice_groups = (int32_t)sg;
+    a.n_slices = (int32_t)((groups + sg - 1) / sg);
+}
+
 // Weight-stationary shape for a launch of a.m tokens: the compiled shapes
-// whose largest panel fits in LDS are scored by the bytes their workgroups
-// read (token rows once per channel group, the panel once per workgroup)
-// spread over the CUs they keep busy, with a small preference for more
-// resident waves a SIMD; SL_PTILE="nt,st,nwv,r" overrides the shape and
-// SL_PSLICES=n the number of token slices (tests: many token groups a wave
-// at small sizes). Fills a's channel-group and slice fields;
-// SL_ERR_UNSUPPORTED when no panel fits.
-static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int32_t run_kind, bool yt, PanelCfg *out,
-                                  size_t *lds_out)
+// whose panel fits in LDS are scored by the bytes their workgroups read
+// (token rows once per channel group, the panel once per workgroup) spread
+// over the CUs they keep busy, with a small preference for more resident
+// waves a SIMD. A byte of row-major X counts three times: a wave's row loads
+// then touch 16 rows an instruction, which runs at about a quarter of the
+// address unit's rate, and idle waves count less (QKV at 384 tokens in rows:
+// 4-tile groups 5.3 us, 2-tile groups, which read the rows twice as often,
+// 8.1). SL_PTILE="nt,st,nwv,r" overrides the shape and SL_PSLICES=n the number
+// of token slices (tests: many token groups a wave at small sizes). Where that picks 6-tile groups, an 8-tile shape takes their place
+//  * for int8 outputs in rows: its 128 channels are whole cache lines of Y,
+//    where 96 leave every line to two workgroups (4096 / 49152 tokens, us:
+//    QKV 15.5 -> 13.5 / 136 -> 104, FFN1 21.0 -> 18.4 / 175 -> 140, BERT-large
+//    FFN1 at 49152 335 -> 222);
+//  * elsewhere, if each SIMD then has less work by over 8 % (the channels
+//    leave a remainder of 6 tiles that 8 divide: BERT-large FFN1 in blocks at
+//    49152 tokens 212 -> 195 us with 17 % less work; with equal work the two
+//    shapes measure within 4 % of each other either way).
+// Fills a's channel-group and slice fields; SL_ERR_UNSUPPORTED when no panel
+// fits.
+static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int32_t run_kind, bool xt, bool yt,
+                                  PanelCfg *out, size_t *lds_out)
 {
     int n_cu = 0, dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    const TileImage &ti = w->tiles;
     const int *e = env_cfg().ptile;
     const PanelCfg forced{e[0], e[1], e[2], e[3]};
     const bool have_forced = e[0] != 0;
-    const int64_t mpad = (a.m + 15) / 16 * 16;
     double best_cost = 0;
     bool found = false;
     for (int ci = 0; ci < kNumPanelCfgs; ++ci) {
         const PanelCfg c = kPanelCfgs[ci];
         if (have_forced && (c.nt != forced.nt || c.st != forced.st || c.nwv != forced.nwv || c.r != forced.r))
             continue;
-        int pi = -1;
-        for (int i = 0; i < w->dev.n_pan; ++i)
-            if (w->dev.pan_nt[i] == c.nt) pi = i;
-        if (pi < 0 || !w->dev.pan_stride[pi]) continue;
-        const int32_t pieces = w->dev.pan_pieces[pi];
-        const size_t lds = panel_lds_bytes(c, run_kind, yt, w->dev.pan_stride[pi]);
+        if (!have_forced && c.nt == 8) continue;  // (below)
+        const uint64_t panel = (uint64_t)ti.n_win * c.nt * kDenseOp;
+        const size_t lds = panel_lds_bytes(c, run_kind, yt, panel);
         if (lds > kLdsMax) continue;
         // resident workgroups per device, cached per (device, shape, LDS size)
         static thread_local struct {
@@ -1056,24 +1011,24 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
             cache_n = cache_n < 16 ? cache_n + 1 : 16;
         }
         if (res < 1) continue;
-        const int64_t n_cg = (w->tiles.n_tiles + c.nt - 1) / c.nt;
-        const int64_t groups = (mpad + c.tg() - 1) / c.tg();
+        const int64_t n_cg = (ti.n_tiles + c.nt - 1) / c.nt;
         // slices: enough workgroups to fill the resident slots once, or one
         // workgroup a CU (fewer panel fills, more token groups a wave),
         // whichever scores better
         for (int64_t want : {res / n_cg, (int64_t)n_cu / n_cg}) {
             want = std::max<int64_t>(1, env_cfg().pslices > 0 ? env_cfg().pslices : want);
-            const int64_t sg = std::max<int64_t>(1, (groups + want - 1) / want);
-            const int64_t n_sl = (groups + sg - 1) / sg;
-            const int64_t nwg = n_cg * n_sl;
+            LinearArgs t = a;
+            set_panel_slices(t, c, n_cg, want);
+            const int64_t nwg = n_cg * t.n_slices;
             if (nwg > 0x7fffffff) continue;
             // busy CUs and the bytes each reads
             const double cus = (double)std::min<int64_t>(n_cu, nwg);
-            const double bytes = (double)a.m * w->k_in * n_cg + (double)nwg * pieces * 16.0;
+            const double bytes = (xt ? 1.0 : 3.0) * (double)a.m * w->k_in * n_cg + (double)nwg * (double)panel;
             // waves per workgroup without a token group idle; among shapes
             // that read the same bytes, more resident waves a SIMD hide more
             // latency
-            const double wave_use = std::min(1.0, (double)sg / c.nwv);
+            double wave_use = std::min(1.0, (double)t.slice_groups / c.nwv);
+            if (!xt) wave_use = std::sqrt(wave_use);
             const double simd_waves = std::min(4.0, (double)std::min<int64_t>(res, nwg) / n_cu * c.nwv / 4.0);
             const double cost = bytes / cus / wave_use / (1.0 + 0.1 * simd_waves);
             if (!found || cost < best_cost) {
@@ -1081,16 +1036,31 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
                 best_cost = cost;
                 *out = c;
                 *lds_out = lds;
-                a.n_cgroups = (int32_t)n_cg;
-                a.n_slices = (int32_t)n_sl;
-                a.slice_groups = (int32_t)sg;
-                a.pan = w->dev.pan[pi];
-                a.pan_bytes = (uint32_t)(n_cg * w->dev.pan_stride[pi]);
-                a.pan_instr = (int32_t)(w->dev.pan_stride[pi] / 1024);
+                a.n_cgroups = t.n_cgroups;
+                a.n_slices = t.n_slices;
+                a.slice_groups = t.slice_groups;
             }
         }
     }
     if (!found) return SL_ERR_UNSUPPORTED;
+    const bool i8 = run_kind != SL_EPI_ACC_I32 && run_kind != SL_EPI_F32 && run_kind != SL_EPI_F32_GELU;
+    if (!have_forced && out->nt == 6 && w->n_out > 96 && env_cfg().pslices == 0) {
+        const bool lines = i8 && !yt && w->n_out % 16 == 0;
+        const PanelCfg c8 = lines ? PanelCfg{8, 2, 8, 2} : PanelCfg{8, 2, 12, 2};
+        const int64_t n_cg = (ti.n_tiles + 7) / 8;
+        const size_t lds = panel_lds_bytes(c8, run_kind, yt, (uint64_t)ti.n_win * 8 * kDenseOp);
+        LinearArgs t = a;
+        set_panel_slices(t, c8, n_cg, std::max<int64_t>(1, n_cu / n_cg));
+        // tile products of the busiest SIMD (a workgroup's groups go round its SIMDs)
+        const auto work = [](const LinearArgs &l, PanelCfg c) { return (l.slice_groups + 3) / 4 * c.nt * c.st; };
+        if (lds <= kLdsMax && (lines || work(t, c8) * 100 < work(a, *out) * 92)) {
+            *out = c8;
+            *lds_out = lds;
+            a.n_cgroups = t.n_cgroups;
+            a.n_slices = t.n_slices;
+            a.slice_groups = t.slice_groups;
+        }
+    }
     return SL_OK;
 }
 
@@ -1118,9 +1088,8 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
     a.n_tiles = ti.n_tiles;
     a.n_win = ti.n_win;
     a.om = nullptr;
-    a.pan = nullptr;
-    a.pan_bytes = 0;
-    a.pan_instr = 0;
+    a.dense = w->dev.dense;
+    a.dense_bytes = w->dev.dense_bytes;
     a.n_slices = 0;
     a.slice_groups = 0;
     a.kw = 0;
@@ -1154,14 +1123,16 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         a.y = static_cast<char *>(y) + (yt ? t0 / 16 * a.y_cb * 512 : t0 * w->n_out * out_bytes);
         a.m = std::min(chunk, m - t0);
         const bool vec = xt || ((w->k_in % 16 == 0) && ((reinterpret_cast<uintptr_t>(a.x) & 15) == 0));
-        // Aligned or block-layout rows: the weight-stationary kernel where it
-        // pays -- a short reduction (at most kPanelMaxWin windows), and a
-        // widening layer (N > K: many channel groups share each token row),
-        // or slices of at least four token groups per wave (the panel filled
-        // once is used for many tokens), or work items of the other kernel
-        // that would not make one round of the CUs keeping most of them
-        // busy -- with the shape the cost model picks; else the
-        // direct-operand kernel (block-layout input, or
+        // Aligned or block-layout rows: the weight-stationary kernel for short
+        // reductions (at most kPanelMaxWin windows), with the shape the cost
+        // model picks (768x768 at 2048 / 4096 tokens, us, against the kernel
+        // it replaced there: int8 blocks 6.2 -> 5.7 / 7.4 -> 6.0, int8 rows
+        // 8.0 -> 6.5 / 10.3 -> 7.7, fp32 rows 7.1 -> 6.2 / 9.2 -> 7.8). Raw
+        // accumulators of block-layout rows take it only for a widening layer
+        // (N > K), slices of at least four token groups a wave, or work items
+        // of the direct kernel that would not make one round of the CUs: else
+        // that kernel is as fast (768x768 at 4096 tokens, 6.8 us both). Longer
+        // reductions: the direct-operand kernel (block-layout input, or
         // block-layout output from aligned rows) or the staged kernel
         // (row-major input and output). SL_PATH=panel|direct|staged forces a
         // kernel (tests, tuning; panel falls back when no panel fits).
@@ -1196,8 +1167,8 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         if (vec && (force_panel || (auto_path && ti.n_win <= kPanelMaxWin))) {
             PanelCfg pc{};
             size_t lds = 0;
-            sl_status pst = choose_panel_cfg(a, w, run_kind, yt, &pc, &lds);
-            if (pst == SL_OK && !force_panel &&
+            sl_status pst = choose_panel_cfg(a, w, run_kind, xt, yt, &pc, &lds);
+            if (pst == SL_OK && !force_panel && xt && kind == SL_EPI_ACC_I32 &&
                 !(w->n_out > w->k_in || a.slice_groups >= 4 * pc.nwv || !one_full_round(direct, a.m, w)))
                 pst = SL_ERR_UNSUPPORTED;
             if (pst == SL_OK) {

@@ -2,26 +2,38 @@
 // token rows that are 16-byte aligned (k_in % 16 == 0) or in SL_LAYOUT_T16X32,
 // when a channel group's whole weight panel fits in LDS.
 //
-// Same method and operand image as the other two kernels (Section "Sparse
-// GEMM operators", Figure 1, Algorithm 1: each stored 4x1 block is a value of
-// the A operand of the 4:2-sparse int8 matrix instruction, the instruction's
-// column indices select the input columns the block mask names, int32
-// accumulation, one fused epilogue per output after the whole reduction).
-// What differs is the schedule. A workgroup owns one channel group (NT
-// 16-channel tiles) and one slice of the tokens. It copies the group's window
-// table and whole panel -- every window's NT main operands and NT overflow
-// operand slots (zeros where a tile has none in the window), laid out that
-// way by the packer -- into LDS once, with no dependent read before the
-// copies, then its waves work through the slice's token groups on their own:
-// a wave loads its token rows (the B operands) straight into registers,
-// R - 1 windows ahead, reads the weight operands from the resident panel a
-// few tiles ahead of its matrix instructions, at offsets that follow from
-// the window alone, and multiplies every slot, so that no per-tile branch or
-// table read sits in the loop (an absent overflow operand is zeros: its
-// products are zero). Past the one barrier that follows the panel copy and
-// the set-up there is none, so one wave's epilogue overlaps the matrix
-// instructions of the others, and the weight image is read from memory once
-// per workgroup rather than once per token tile.
+// Same product as the other kernels (Section "Sparse GEMM operators", Figure
+// 1, Algorithm 1: int8 products of the stored weight blocks with the input
+// columns their mask names, int32 accumulation, one fused epilogue per output
+// after the whole reduction), from the dense operand image: the stored blocks
+// at their places in A operands of v_mfma_i32_16x16x64_i8, zeros elsewhere.
+// The 4:2-sparse form needs an overflow operand beside the main one in 37 %
+// of the (tile, window) pairs at 90 % sparsity and in 97 % at 80 %, and a
+// branch per pair costs more than it saves, so both were multiplied: the same
+// matrix time as the dense operands, 6 % more bytes, two index reads a tile,
+// and twice the vector issue slots (a matrix instruction takes 8.7 cycles of
+// them from the other waves of its SIMD in the sparse form, 4.7 in the dense
+// one, measured beside a wave of fused multiply-adds).
+//
+// A workgroup owns one channel group (NT 16-channel tiles) and one slice of
+// the tokens. It copies the group's panel into LDS once (back-to-back copies,
+// nothing read before them), then its waves work through the slice's token
+// groups on their own: a wave loads its token rows (the B operands) straight
+// into registers, R - 1 windows ahead, and reads the weight operands from the
+// resident panel three ahead of the matrix instructions that use them. Past
+// the one barrier that follows the panel copy and the set-up there is none,
+// so one wave's epilogue overlaps the matrix instructions of the others, and
+// the weight image is read from memory once per workgroup rather than once
+// per token tile.
+//
+// What bounds it: each wave's chain of matrix instructions and then epilogue,
+// with two or three waves a SIMD to overlap them (at 49152 tokens FFN1's
+// matrix instructions take 55 of its 114 us at the 2.13 GHz it runs at, its
+// vector instructions about as much; timing copies without the output stores,
+// the cache misses of the token rows or the LDS reads of the weights are less
+// than 3 % faster, one without the epilogue's arithmetic 24 %). Measured, us,
+// 4:2-sparse operands -> dense: 4096 tokens, blocks: FFN1 at 90 % 14.4 ->
+// 12.6, QKV at 80 % 12.4 -> 10.7; 49152 tokens: FFN1 139 -> 110, QKV 99 -> 79.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,26 +48,25 @@ struct PShape {
     static constexpr int NTH = 64 * NWV;
     static constexpr int TG = 16 * ST;             // tokens per group
     static constexpr int VEC = 2 * NT * kTileN * 4;  // the group's scales sx * sw[n], then its biases
+    static constexpr int WB = NT * kDenseOp;         // panel bytes of one window
+    static constexpr int WC = WB / 1024;             // 1024-byte copies of one window
     // per wave: 16 token rows of 32 four-byte outputs (two tiles), padded to
     // 36 words so that neither the writes nor the reads of the transpose meet
     // a bank twice in one pass
     static constexpr int TRW = 36;
     static constexpr int TR = 16 * TRW * 4;
-    static_assert(NT <= 32, "an overflow mask has 32 bits");
+    static_assert(NT % 2 == 0 && ST % 2 == 0, "the int8 store takes four fragments");
 };
 
-// int32 / fp32 outputs in rows, and int8 outputs in the block layout, go
-// through a per-wave LDS transpose
+// int32 / fp32 outputs in rows go through a per-wave LDS transpose
 template <int KIND, bool YT, int NT>
 constexpr bool panel_transposes()
 {
-    return NT % 2 == 0 && ((EpiOut<KIND>::kBytes == 4 && KIND != SL_EPI_F32_GELU && !YT) ||
-                           (EpiOut<KIND>::kBytes == 1 && YT));
+    return NT % 2 == 0 && EpiOut<KIND>::kBytes == 4 && KIND != SL_EPI_F32_GELU && !YT;
 }
 
 // LDS layout: weight scales and biases | GELU step table | per-wave transpose
-// areas | window table (n_win + 1 entries of 16 bytes) and panel, as one
-// stride of the panel image
+// areas | panel
 template <int KIND, int NT, int ST, int NWV, bool YT>
 struct PLds {
     using S = PShape<NT, ST, NWV>;
@@ -63,7 +74,7 @@ struct PLds {
     static constexpr int kTr = panel_transposes<KIND, YT, NT>() ? NWV * S::TR : 0;
     static constexpr int kFixed = S::VEC + kTab + kTr;
     static_assert(kFixed % 16 == 0, "the copies write 16-byte pieces");
-    static size_t bytes(uint32_t stride) { return (size_t)kFixed + stride; }
+    static size_t bytes(uint64_t panel) { return (size_t)kFixed + panel; }
 };
 
 // Calls f(std::integral_constant<int, 0>) .. f(std::integral_constant<int, N-1>) in order.
@@ -101,24 +112,28 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     float *const vec = reinterpret_cast<float *>(smem);
     GeluCell *const tab = reinterpret_cast<GeluCell *>(smem + S::VEC);
     int8_t *const trans = smem + S::VEC + L::kTab + wave * S::TR;
-    int8_t *const panel = smem + L::kFixed + (a.n_win + 1) * 16;
+    int8_t *const panel = smem + L::kFixed;
 
-    // ---- the group's window table and panel: one stride of the panel image,
-    // copied global to LDS (no registers) in 1024-byte instructions, wave v
-    // issuing instructions v, v + NWV, ...; nothing is read before them, so
-    // the copies start at once and land while the set-up runs
+    // ---- the group's panel: [window][tile] pairs of operands, copied global
+    // to LDS (no registers) in 1024-byte instructions, wave v issuing
+    // instructions v, v + NWV, ...; nothing is read before them, so the copies
+    // start at once and land while the set-up runs. (Tiles past the last one
+    // read the next window's, or zeros past the image: their channels are
+    // never stored.)
     {
         constexpr int kMaxCopies = (int)((kLdsMax / 1024 + NWV - 1) / NWV);
         const __amdgpu_buffer_rsrc_t ir =
-            __builtin_amdgcn_make_buffer_rsrc((void *)a.pan, 0, (int)a.pan_bytes, kRsrcWord3);
-        const uint32_t src = (uint32_t)cg * (uint32_t)a.pan_instr * 1024u + (uint32_t)lane * 16u;
-        int8_t *const dst = smem + L::kFixed;
+            __builtin_amdgcn_make_buffer_rsrc((void *)a.dense, 0, (int)a.dense_bytes, kRsrcWord3);
+        const uint32_t src = (uint32_t)tile0 * kDenseOp + (uint32_t)lane * 16u;
+        const uint32_t wstride = (uint32_t)a.n_tiles * kDenseOp;
+        const int n_copies = a.n_win * S::WC;
 #pragma unroll
         for (int i = 0; i < kMaxCopies; ++i) {
             const int j = wave + i * NWV;
-            if (j < a.pan_instr)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(ir, (lds_void *)(dst + (size_t)j * 1024), 16,
-                                                         src + (uint32_t)j * 1024u, 0, 0, 0);
+            if (j < n_copies)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    ir, (lds_void *)(panel + (size_t)j * 1024), 16,
+                    src + (uint32_t)(j / S::WC) * wstride + (uint32_t)(j % S::WC) * 1024u, 0, 0, 0);
         }
     }
 
@@ -152,13 +167,12 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
                 ro[s] = r < a.m ? (uint32_t)(r * a.k) + 32u * (uint32_t)(lane >> 4) : kOob;
         }
     };
-    // (valid false: every lane reads zeros; the loads are issued all the
-    // same, so that the number of loads in flight is the same on every path
-    // and the compiler's waits on them stay exact)
-    auto load_rows = [&](i32x8 (&bv)[ST], const uint32_t (&ro)[ST], int w, bool valid = true) {
+    // (an offset of kOob plus a window's stays past the buffer: such a lane
+    // reads zeros)
+    auto load_rows = [&](i32x8 (&bv)[ST], const uint32_t (&ro)[ST], int w) {
 #pragma unroll
         for (int s = 0; s < ST; ++s) {
-            const uint32_t off = !valid || ro[s] == kOob ? kOob : ro[s] + (uint32_t)w * (XT ? 4 * 512 : kWin);
+            const uint32_t off = ro[s] + (uint32_t)w * (XT ? 4 * 512 : kWin);
             const i32x4 lo = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
             const i32x4 hi = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off + 16u, 0, 0));
             bv[s] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -169,60 +183,39 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     i32x8 bv[R][ST];
     static_assert(R >= 2, "at least one window loads while another is multiplied");
 
-    // Weight operands in registers, a ring of RS tiles (main operand,
-    // overflow slot and their index words) filled LA tiles ahead of the
-    // matrix instructions: while tile c of window u is multiplied, tile
-    // c + LA of the wave's tile stream is read (of window u, else of window
-    // u + 1; past the group's last window that is the first window of the
-    // next group, which uses the same panel). A tile's slot is its place in
-    // the stream modulo RS; RS divides 2 NT and windows are walked in pairs,
-    // so the slot follows from c and the window's parity. Three tiles in
-    // flight (NT = 6) instead of two whole windows leave about 90 registers
-    // for more waves a SIMD; small tile groups keep a whole window ahead, so
-    // that the reads have as many matrix instructions to hide behind.
-    constexpr int RS = NT % 3 == 0 ? 3 : (NT <= 2 ? 2 * NT : NT);
-    constexpr int LA = RS - 1 < NT ? RS - 1 : NT;
-    static_assert((2 * NT) % RS == 0 && LA >= 1, "ring slots follow from the tile and the window's parity");
-    struct TOp {
-        i32x4 av, ao;
-        int ix, io;
+    // Weight operands in registers, a ring of RS units (one half-window of one
+    // tile each) filled LA units ahead of the matrix instructions: while unit
+    // c of window u is multiplied, unit c + LA of the wave's stream is read
+    // (of window u, else of window u + 1; past the group's last window that
+    // is the first window of the next group, which uses the same panel). RS
+    // divides the units of a window, so a unit's slot is c % RS.
+    constexpr int NU = 2 * NT;
+    constexpr int RS = 4;
+    constexpr int LA = RS - 1;
+    static_assert(NU % RS == 0 && LA >= 1, "ring slots follow from the unit");
+    i32x4 ring[RS];
+    auto read_unit = [&](i32x4 &t, uint32_t base, int c) {
+        t = *reinterpret_cast<const i32x4 *>(panel + base + (2 * (c % NT) + c / NT) * 1024 + lane * 16);
     };
-    TOp ring[RS];
-    auto read_tile = [&](TOp &t, uint32_t base, int c) {
-        const int8_t *const wb = panel + base + c * kOpBytes;
-        t.av = *reinterpret_cast<const i32x4 *>(wb + lane * 16);
-        t.ix = *reinterpret_cast<const int *>(wb + 1024 + iword * 4);
-        const int8_t *const oo = panel + base + (NT + c) * kOpBytes;
-        t.ao = *reinterpret_cast<const i32x4 *>(oo + lane * 16);
-        t.io = *reinterpret_cast<const int *>(oo + 1024 + iword * 4);
-    };
-    // window u (parity PAR; token rows in ring slot PB, panel bytes cbase;
-    // the next window's at nbase)
-    auto multiply = [&](auto par, auto pb, uint32_t cbase, uint32_t nbase) {
-        constexpr int PAR = decltype(par)::value;
+    // window u (token rows in ring slot PB, panel bytes cbase; the next
+    // window's at nbase)
+    auto multiply = [&](auto pb, uint32_t cbase, uint32_t nbase) {
         constexpr int PB = decltype(pb)::value;
-        static_for<NT>([&](auto cc) {
+        static_for<NU>([&](auto cc) {
             constexpr int C = decltype(cc)::value;
             constexpr int J = C + LA;
-            if constexpr (J < NT)
-                read_tile(ring[(PAR * NT + J) % RS], cbase, J);
+            if constexpr (J < NU)
+                read_unit(ring[J % RS], cbase, J);
             else
-                read_tile(ring[(PAR * NT + J) % RS], nbase, J - NT);
-            TOp &t = ring[(PAR * NT + C) % RS];
+                read_unit(ring[J % RS], nbase, J - NU);
 #pragma unroll
-            for (int s = 0; s < ST; ++s)
-                acc[C][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(t.av, bv[PB][s], acc[C][s], t.ix, 0, 0);
-#pragma unroll
-            for (int s = 0; s < ST; ++s)
-                acc[C][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(t.ao, bv[PB][s], acc[C][s], t.io, 0, 0);
-            // the four operand reads spread over the tile's matrix
-            // instructions, so that a read waiting for room in the LDS queue
-            // does not leave the matrix core idle
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);       // one LDS read
-                __builtin_amdgcn_sched_group_barrier(0x008, ST / 2, 0);  // matrix instructions
+            for (int s = 0; s < ST; ++s) {
+                const i32x4 b = C < NT ? __builtin_shufflevector(bv[PB][s], bv[PB][s], 0, 1, 2, 3)
+                                           : __builtin_shufflevector(bv[PB][s], bv[PB][s], 4, 5, 6, 7);
+                acc[C % NT][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ring[C % RS], b, acc[C % NT][s], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+            __builtin_amdgcn_sched_group_barrier(0x008, ST, 0);  // its matrix instructions
         });
     };
 
@@ -250,60 +243,65 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
         // written too
         const int64_t mlim = YT ? mpad : a.m;
         const bool whole = t0 + S::TG <= mlim && (tile0 + NT) * kTileN <= a.n;
-        if constexpr (EpiOut<KIND>::kBytes == 1 && YT && panel_transposes<KIND, YT, NT>()) {
-            if (whole && tile0 % 2 == 0) {
-                // int8 codes in the block layout: a lane holds 4 channels of
-                // one token, half of a 32-byte block row; each pair of tiles
-                // fills one 512-byte block (16 tokens x 32 channels), which
-                // goes through this wave's LDS area so that the store writes
-                // the whole block, 8 contiguous bytes a lane
-                uint32_t *const tr = reinterpret_cast<uint32_t *>(trans);
-                const int wi = (lane & 15) * 8 + (lane >> 4);  // word: token l%16, channels 4(l/16)..
+        if constexpr (EpiOut<KIND>::kBytes == 1) {
+            if (whole && (YT || (a.n % 16 == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0))) {
+                // int8 codes: a lane holds 4 channels of one token, and four
+                // fragments (a tile of a subtile each) are transposed across
+                // the four lane groups in registers, after which lane group g
+                // holds the 16 channels of fragment g: 16 contiguous bytes a
+                // lane, in either layout.
                 int8_t *const y8 = static_cast<int8_t *>(a.y);
+                const int g = lane >> 4, t = lane & 15;
+                // fragments: four tiles of one subtile, or (Q) two tiles of two
+                auto quad = [&](auto c0, auto s0, auto two) {
+                    constexpr int C0 = decltype(c0)::value, S0 = decltype(s0)::value;
+                    constexpr bool Q = decltype(two)::value;
+                    uint32_t v[4];
+                    // (two fragments at a time: the GELU kind's table reads
+                    // of 8 outputs a lane are in flight together)
 #pragma unroll
-                for (int c = 0; c < NT; c += 2) {
-                    float s0[4], b0[4], s1[4], b1[4];
-                    scales(c, s0, b0);
-                    scales(c + 1, s1, b1);
-                    // the GELU kind's table reads for the pair's ST subtiles
-                    // are issued together, so that their LDS latency (and
-                    // bank conflicts: the cells are data-dependent) is met
-                    // once per pair rather than once per two outputs
-                    [[maybe_unused]] float gy[ST][2][4];
-                    [[maybe_unused]] u32x2 gcell[ST][2][4];
-                    if constexpr (KIND == SL_EPI_I8_GELU) {
-                        uint32_t ad[ST][2][4];
-#pragma unroll
-                        for (int st = 0; st < ST; ++st) {
-                            gelu_cells(acc[c][st], s0, b0, tab, hinv, eoff, cmax, gy[st][0], ad[st][0]);
-                            gelu_cells(acc[c + 1][st], s1, b1, tab, hinv, eoff, cmax, gy[st][1], ad[st][1]);
-                        }
-#pragma unroll
-                        for (int st = 0; st < ST; ++st)
-#pragma unroll
-                            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) gcell[st][h][r] = lds_read_u2(ad[st][h][r]);
-                    }
-#pragma unroll
-                    for (int st = 0; st < ST; ++st) {
-                        uint32_t v0, v1;
+                    for (int h = 0; h < 2; ++h) {
+                        const int ca = C0 + (Q ? 0 : 2 * h), sa = S0 + (Q ? h : 0);
+                        float s0[4], b0[4], s1[4], b1[4];
+                        scales(ca, s0, b0);
+                        scales(ca + 1, s1, b1);
                         if constexpr (KIND == SL_EPI_I8_GELU) {
-                            v0 = gelu_codes(gy[st][0], gcell[st][0]);
-                            v1 = gelu_codes(gy[st][1], gcell[st][1]);
+                            float gy[2][4];
+                            uint32_t ad[2][4];
+                            u32x2 cell[2][4];
+                            gelu_cells(acc[ca][sa], s0, b0, tab, hinv, eoff, cmax, gy[0], ad[0]);
+                            gelu_cells(acc[ca + 1][sa], s1, b1, tab, hinv, eoff, cmax, gy[1], ad[1]);
+#pragma unroll
+                            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) cell[j][r] = lds_read_u2(ad[j][r]);
+                            v[2 * h] = gelu_codes(gy[0], cell[0]);
+                            v[2 * h + 1] = gelu_codes(gy[1], cell[1]);
                         } else {
-                            v0 = epilogue_value<KIND>(a, acc[c][st], s0, b0, tab, hinv, eoff, cmax);
-                            v1 = epilogue_value<KIND>(a, acc[c + 1][st], s1, b1, tab, hinv, eoff, cmax);
+                            v[2 * h] = epilogue_value<KIND>(a, acc[ca][sa], s0, b0, tab, hinv, eoff, cmax);
+                            v[2 * h + 1] = epilogue_value<KIND>(a, acc[ca + 1][sa], s1, b1, tab, hinv, eoff, cmax);
                         }
-                        // (a wave's LDS operations take effect in order: the
-                        // previous block's read is done before these writes)
-                        tr[wi] = v0;
-                        tr[wi + 4] = v1;
-                        const uint2 r = *reinterpret_cast<const uint2 *>(tr + 2 * lane);
-                        int8_t *const p = y8 + t16x32_offset(t0 + st * 16, (tile0 + c) * kTileN, a.y_cb) + 8 * lane;
-                        store_nt(p, i32x2{(int)r.x, (int)r.y});
                     }
-                }
+                    transpose4(v);
+                    int8_t *p;
+                    if constexpr (YT)
+                        p = y8 + ((t0 / 16 + S0) * a.y_cb + (tile0 + C0) / 2) * 512 +
+                            (uint32_t)((g >> 1) * (Q ? a.y_cb * 512 : 512) + t * 32 + (g & 1) * 16);
+                    else
+                        p = y8 + (t0 + S0 * 16) * a.n + (tile0 + C0) * kTileN +
+                            (uint32_t)((t + (Q ? (g >> 1) * 16 : 0)) * a.n + (Q ? g & 1 : g) * 16);
+                    store_nt(p, i32x4{(int)v[0], (int)v[1], (int)v[2], (int)v[3]});
+                };
+                static_for<NT / 4>([&](auto cq) {
+                    static_for<ST>([&](auto sq) {
+                        quad(std::integral_constant<int, 4 * decltype(cq)::value>{}, sq, std::false_type{});
+                    });
+                });
+                if constexpr (NT % 4 != 0)
+                    static_for<ST / 2>([&](auto sq) {
+                        quad(std::integral_constant<int, NT / 4 * 4>{},
+                             std::integral_constant<int, 2 * decltype(sq)::value>{}, std::true_type{});
+                    });
                 return;
             }
         } else if constexpr (panel_transposes<KIND, YT, NT>()) {
@@ -382,36 +380,24 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     // R-window ring, so the u-th window of every group uses ring slot u % R.
     // Before multiplying element e the wave starts loading element e + R - 1
     // (possibly a window of its next group), so the next group's first
-    // windows load during the current group's epilogue. The workgroups that
-    // share a token slice (one per channel group, on one XCD) would otherwise
-    // read the same rows at the same moment: each workgroup visits the
-    // slice's groups from its own starting point and each wave walks the
-    // windows from its own starting point (int32 sums do not depend on the
-    // order).
+    // windows load during the current group's epilogue. (Starting each
+    // workgroup and wave at a group and window of its own, so that those that
+    // share token rows read them at different times, changes nothing.)
     const int n_my = n_groups > wave ? (n_groups - wave + NWV - 1) / NWV : 0;
     const int nwp = (a.n_win + R - 1) / R * R;
-    const int rot_g = n_groups > 0 ? (int)(((int64_t)cg * 5) % n_groups) : 0;
-    const int rot_w = (int)(((int64_t)cg + wave) % a.n_win);
     auto group_t0 = [&](int i) {
-        int g = wave + i * NWV + rot_g;
-        g = g >= n_groups ? g - n_groups : g;
-        return slice0 + (int64_t)g * S::TG;
-    };
-    auto phys = [&](int u) {
-        const int p = u + rot_w;
-        return p >= a.n_win ? p - a.n_win : p;
+        return slice0 + (int64_t)(wave + i * NWV) * S::TG;
     };
     uint32_t ro[ST], ron[ST];
-    // panel byte of the element at window u: NT main operands and NT
-    // overflow slots per window
-    auto wbase = [&](int u) { return (uint32_t)phys(u) * (uint32_t)(2 * NT * kOpBytes); };
+    // panel byte of window u
+    auto wbase = [&](int u) { return (uint32_t)u * (uint32_t)S::WB; };
     // the first R - 1 windows of token rows load while the panel copies are
     // in flight, then the set-up; one barrier after all of them, past which
     // table, panel, scales and GELU table are in LDS
     row_offsets(n_my > 0 ? group_t0(0) : slice0, ro);
     static_for<R - 1>([&](auto uc) {
         constexpr int U = decltype(uc)::value;
-        load_rows(bv[U], ro, U < a.n_win ? phys(U) : 0, n_my > 0 && U < a.n_win);
+        load_rows(bv[U], ro, U);
     });
     // ---- set-up: scales and biases, GELU table
     static_assert(NT * kTileN <= S::NTH, "one scale and one bias a thread");
@@ -434,13 +420,12 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     __syncthreads();
     if (n_my > 0) {
 #pragma unroll
-        for (int j = 0; j < LA; ++j) read_tile(ring[j], wbase(0), j);
+        for (int j = 0; j < LA; ++j) read_unit(ring[j], wbase(0), j);
     }
-    static_assert(R % 2 == 0, "ring slots and operand sets alternate together");
-    for (int i = 0; i < n_my; ++i) {
+        for (int i = 0; i < n_my; ++i) {
         const int64_t t0 = group_t0(i);
         const bool has_next = i + 1 < n_my;
-        if (has_next) row_offsets(group_t0(i + 1), ron);
+        row_offsets(has_next ? group_t0(i + 1) : mpad, ron);
 #pragma unroll
         for (int c = 0; c < NT; ++c)
 #pragma unroll
@@ -451,30 +436,20 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
                 constexpr int PS = (U + R - 1) % R;
                 const int u = wb + U;
                 const int pu = u + R - 1;
-                const bool in_cur = pu < a.n_win;
-                const int pn = pu - nwp;  // window of the next group, if >= 0
-                const bool in_next = has_next && pn >= 0 && pn < a.n_win;
+                // past the group's windows: the next group's (rows past the
+                // last group read zeros)
+                const bool in_cur = pu < nwp;
                 uint32_t rs[ST];
 #pragma unroll
                 for (int s = 0; s < ST; ++s) rs[s] = in_cur ? ro[s] : ron[s];
-                load_rows(bv[PS], rs, in_cur ? phys(pu) : (in_next ? phys(pn) : 0), in_cur || in_next);
+                load_rows(bv[PS], rs, in_cur ? pu : pu - nwp);
                 if (u < a.n_win) {
                     // the ring reads ahead into this group's next window,
                     // else the next group's first (a stale read past the
                     // last group)
-                    multiply(std::integral_constant<int, U % 2>{}, uc, wbase(u), wbase(u + 1 < a.n_win ? u + 1 : 0));
+                    multiply(uc, wbase(u), wbase(u + 1 < a.n_win ? u + 1 : 0));
                 }
             });
-        }
-        // after an odd number of windows the next group's first tiles sit
-        // NT slots on; move them to where its first window reads them
-        if constexpr (NT % RS != 0) {
-            if (a.n_win & 1) {
-                static_for<LA>([&](auto tc) {
-                    constexpr int T = decltype(tc)::value;
-                    ring[T % RS] = ring[(NT + T) % RS];
-                });
-            }
         }
         epilogue(t0);
         if (has_next) {
@@ -538,7 +513,9 @@ static sl_status launch_panel_cfg(const LinearArgs &a, const GeluArg *ep, size_t
     F(6, 2, 8, 2)          \
     F(4, 2, 8, 2)          \
     F(2, 2, 8, 4)          \
-    F(2, 4, 4, 2)
+    F(2, 4, 4, 2)          \
+    F(8, 2, 8, 2)         \
+    F(8, 2, 12, 2)
 
 const PanelCfg kPanelCfgs[kNumPanelCfgs] = {
 #define SL_PANEL_ENTRY(NT_, ST_, NWV_, R_) {NT_, ST_, NWV_, R_},
@@ -560,26 +537,26 @@ static sl_status launch_panel_kind(const LinearArgs &a, const GeluArg *ep, Panel
 }
 
 template <int KIND>
-static size_t panel_lds_kind(PanelCfg c, bool yt, uint32_t stride)
+static size_t panel_lds_kind(PanelCfg c, bool yt, uint64_t panel)
 {
 #define SL_PANEL_LDS(NT_, ST_, NWV_, R_)                                                          \
     if (c.nt == NT_ && c.st == ST_ && c.nwv == NWV_ && c.r == R_)                                 \
-        return yt ? PLds<KIND, NT_, ST_, NWV_, true>::bytes(stride)                               \
-                  : PLds<KIND, NT_, ST_, NWV_, false>::bytes(stride);
+        return yt ? PLds<KIND, NT_, ST_, NWV_, true>::bytes(panel)                               \
+                  : PLds<KIND, NT_, ST_, NWV_, false>::bytes(panel);
     SL_PANEL_SHAPES(SL_PANEL_LDS)
 #undef SL_PANEL_LDS
     return (size_t)-1;
 }
 
-size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, bool yt, uint32_t stride)
+size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, bool yt, uint64_t panel)
 {
     switch (run_kind) {
-    case SL_EPI_ACC_I32: return panel_lds_kind<SL_EPI_ACC_I32>(c, false, stride);
-    case SL_EPI_F32: return panel_lds_kind<SL_EPI_F32>(c, false, stride);
-    case SL_EPI_F32_GELU: return panel_lds_kind<SL_EPI_F32_GELU>(c, false, stride);
-    case SL_EPI_I8: return panel_lds_kind<SL_EPI_I8>(c, yt, stride);
-    case SL_EPI_I8_GELU: return panel_lds_kind<SL_EPI_I8_GELU>(c, yt, stride);
-    default: return panel_lds_kind<kEpiI8GeluErf>(c, yt, stride);
+    case SL_EPI_ACC_I32: return panel_lds_kind<SL_EPI_ACC_I32>(c, false, panel);
+    case SL_EPI_F32: return panel_lds_kind<SL_EPI_F32>(c, false, panel);
+    case SL_EPI_F32_GELU: return panel_lds_kind<SL_EPI_F32_GELU>(c, false, panel);
+    case SL_EPI_I8: return panel_lds_kind<SL_EPI_I8>(c, yt, panel);
+    case SL_EPI_I8_GELU: return panel_lds_kind<SL_EPI_I8_GELU>(c, yt, panel);
+    default: return panel_lds_kind<kEpiI8GeluErf>(c, yt, panel);
     }
 }
 

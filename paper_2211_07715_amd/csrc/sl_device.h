@@ -15,6 +15,7 @@ namespace sl {
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
 
 // Output store marked non-temporal: a kernel's outputs are read by a later
 // kernel, never by itself, so they need not displace its inputs in the caches.
@@ -59,7 +60,7 @@ struct LinearArgs {
     int32_t n;
     int32_t k;
     const int8_t *main;
-    const int8_t *ovf;    // compact overflow operands (staged, weight-stationary kernels) or the dense
+    const int8_t *ovf;    // compact overflow operands (staged kernel) or the dense
                           // overflow image (split-reduction, direct kernels)
     uint32_t main_bytes;  // image sizes: the range of the buffer loads
     uint32_t ovf_bytes;
@@ -75,10 +76,8 @@ struct LinearArgs {
     int32_t x_cb;       // 32-feature column blocks of x (SL_LAYOUT_T16X32 input)
     int32_t y_cb;       // 32-channel column blocks of y (SL_LAYOUT_T16X32 output)
     // weight-stationary kernel only
-    const int8_t *pan;      // panel image of this launch's channel-group size: per group, its window
-                            // table ([n_win + 1][4] words) and panel, pan_instr KiB apart
-    uint32_t pan_bytes;     // bytes of that image (the range of the copies)
-    int32_t pan_instr;      // 1024-byte copies per channel group
+    const int8_t *dense;    // dense operand image [n_win][n_tiles][kDenseOp]
+    uint32_t dense_bytes;   // its size (the range of the copies)
     int32_t n_slices;       // token slices per channel group
     int32_t slice_groups;   // token groups (16 ST tokens) per slice
     // split-reduction kernel only: waves per workgroup
@@ -131,6 +130,41 @@ __device__ __forceinline__ int32_t requant_i8(float g, float inv_so)
     float r = __builtin_rintf(v);
     r = fminf(fmaxf(r, -127.0f), 127.0f);
     return (int32_t)r;
+}
+
+// The same code in the low byte of a word (the others unspecified), two
+// instructions after the product: clamping to whole bounds first gives the
+// same rounding, and adding 1.5 * 2^23 rounds to the nearest even integer,
+// whose two's complement the sum's low bits are. (A NaN gives -127, as above.)
+__device__ __forceinline__ uint32_t requant_bits(float g, float inv_so)
+{
+#pragma clang fp contract(off)
+    return __float_as_uint(__builtin_amdgcn_fmed3f(g * inv_so, -127.0f, 127.0f) + 12582912.0f);
+}
+__device__ __forceinline__ uint32_t pack_bytes(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3)
+{
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(b3, b2, 0x0c0c0400u),
+                                 __builtin_amdgcn_perm(b1, b0, 0x0c0c0400u), 0x05040100u);
+}
+
+// 4 x 4 transpose of words across the wave's four 16-lane groups: lane group
+// g's word j becomes lane group j's word g, lane by lane.
+__device__ __forceinline__ void transpose4(uint32_t (&v)[4])
+{
+    auto s32 = [](uint32_t &x, uint32_t &y) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    };
+    auto s16 = [](uint32_t &x, uint32_t &y) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    };
+    s32(v[0], v[2]);
+    s32(v[1], v[3]);
+    s16(v[0], v[1]);
+    s16(v[2], v[3]);
 }
 
 // Value stored for one accumulator group (4 channels of one token): int32
@@ -235,10 +269,8 @@ __device__ __forceinline__ typename EpiOut<KIND>::T epilogue_value_s(float inv_s
         if constexpr (KIND == SL_EPI_F32 || KIND == SL_EPI_F32_GELU) {
             return make_float4(g[0], g[1], g[2], g[3]);
         } else {
-            uint32_t packed = 0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) packed |= ((uint32_t)requant_i8(g[r], inv_so) & 0xffu) << (8 * r);
-            return packed;
+            return pack_bytes(requant_bits(g[0], inv_so), requant_bits(g[1], inv_so), requant_bits(g[2], inv_so),
+                              requant_bits(g[3], inv_so));
         }
     }
 }
@@ -372,11 +404,10 @@ struct PanelCfg {
     int nt, st, nwv, r;
     int tg() const { return 16 * st; }
 };
-constexpr int kNumPanelCfgs = 5;
+constexpr int kNumPanelCfgs = 7;
 extern const PanelCfg kPanelCfgs[kNumPanelCfgs];
-// LDS bytes of a panel kernel launch whose channel groups' tables and panels
-// take `stride` bytes each
-size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, bool yt, uint32_t stride);
+// LDS bytes of a panel kernel launch whose panel takes `panel` bytes
+size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, bool yt, uint64_t panel);
 sl_status launch_panel(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, PanelCfg c, bool xt, bool yt,
                        size_t lds, hipStream_t stream);
 // resident workgroups of a panel-kernel shape for `lds` bytes of LDS (all kinds and layouts of a

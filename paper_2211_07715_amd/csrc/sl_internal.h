@@ -85,14 +85,11 @@ int gelu_table_code(const GeluTable &t, float y);
 // operand of the window. Layout [n_win][n_groups][2] uint32.
 constexpr int kMaxOmTables = 8;
 
-// Weight panels of the weight-stationary kernel, per tile-group size nt: for
-// channel group g and window w, the entry {mask, first, base, 0} at
-// [g][n_win + 1][4] uint32: mask and first as in the overflow table; base =
-// offset, in 16-byte pieces, of the window's operands in the group's panel
-// (the nt main operands, then nt overflow operand slots, one per tile, zeros
-// where the tile has none: base = w * 2 * nt * 68). Entry n_win holds the
-// panel's total size in its base word.
-constexpr int kMaxPanTables = 4;
+// One operand of the dense operand image [n_win][n_tiles]: a tile's 16
+// channels x one window, as two A operands of v_mfma_i32_16x16x64_i8 (1024
+// bytes each, lane-major): byte 16 l + i of half h is channel l % 16, window
+// column 32 (l / 16) + 16 h + i. The weight-stationary kernel reads it.
+constexpr uint32_t kDenseOp = 2048;
 
 struct DeviceImage {
     int device = -1;
@@ -105,16 +102,8 @@ struct DeviceImage {
     int32_t n_om = 0;
     int32_t om_nt[kMaxOmTables] = {};
     const uint32_t *om[kMaxOmTables] = {};
-    int32_t n_pan = 0;
-    int32_t pan_nt[kMaxPanTables] = {};
-    int32_t pan_pieces[kMaxPanTables] = {};  // largest panel over the groups, 16-byte pieces
-    // per channel-group size: each group's window table ([n_win + 1][4]
-    // words: overflow mask, first overflow operand, panel offset in pieces)
-    // followed by its panel, byte for byte as the weight-stationary kernel
-    // holds them in LDS, groups pan_stride bytes apart (a multiple of 1024;
-    // 0: the panels do not fit in LDS and there is no such image)
-    uint32_t pan_stride[kMaxPanTables] = {};
-    const int8_t *pan[kMaxPanTables] = {};
+    const int8_t *dense = nullptr;
+    uint32_t dense_bytes = 0;
     // split-reduction kernel: the overflow operands in the main image's
     // order, one slot per (window, tile), zeros where the tile has none
     const int8_t *ovfd = nullptr;
