@@ -974,7 +974,7 @@ static void set_panel_slices(LinearArgs &a, PanelCfg c, int64_t n_cg, int64_t wa
 //    shapes measure within 4 % of each other either way).
 // Fills a's channel-group and slice fields; SL_ERR_UNSUPPORTED when no panel
 // fits.
-static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int32_t run_kind, bool xt, bool yt,
+static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int32_t run_kind, RowsAt xl, bool yt,
                                   PanelCfg *out, size_t *lds_out)
 {
     int n_cu = 0, dev = 0;
@@ -990,7 +990,8 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
         const PanelCfg c = kPanelCfgs[ci];
         if (have_forced && (c.nt != forced.nt || c.st != forced.st || c.nwv != forced.nwv || c.r != forced.r))
             continue;
-        if (!have_forced && c.nt == 8) continue;  // (below)
+        const bool bytes_at = xl == RowsAt::kBytes;
+        if (bytes_at ? !panel_takes_bytes(c.nt, c.st, c.nwv, c.r) : !have_forced && c.nt == 8) continue;  // (8: below)
         const uint64_t panel = (uint64_t)ti.n_win * c.nt * kDenseOp;
         const size_t lds = panel_lds_bytes(c, run_kind, yt, panel);
         if (lds > kLdsMax) continue;
@@ -1023,12 +1024,12 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
             if (nwg > 0x7fffffff) continue;
             // busy CUs and the bytes each reads
             const double cus = (double)std::min<int64_t>(n_cu, nwg);
-            const double bytes = (xt ? 1.0 : 3.0) * (double)a.m * w->k_in * n_cg + (double)nwg * (double)panel;
+            const double bytes = (xl == RowsAt::kBlocks ? 1.0 : 3.0) * (double)a.m * w->k_in * n_cg + (double)nwg * (double)panel;
             // waves per workgroup without a token group idle; among shapes
             // that read the same bytes, more resident waves a SIMD hide more
             // latency
             double wave_use = std::min(1.0, (double)t.slice_groups / c.nwv);
-            if (!xt) wave_use = std::sqrt(wave_use);
+            if (xl != RowsAt::kBlocks) wave_use = std::sqrt(wave_use);
             const double simd_waves = std::min(4.0, (double)std::min<int64_t>(res, nwg) / n_cu * c.nwv / 4.0);
             const double cost = bytes / cus / wave_use / (1.0 + 0.1 * simd_waves);
             if (!found || cost < best_cost) {
@@ -1045,7 +1046,7 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
     if (!found) return SL_ERR_UNSUPPORTED;
     const bool i8 = run_kind != SL_EPI_ACC_I32 && run_kind != SL_EPI_F32 && run_kind != SL_EPI_F32_GELU;
     if (!have_forced && out->nt == 6 && w->n_out > 96 && env_cfg().pslices == 0) {
-        const bool lines = i8 && !yt && w->n_out % 16 == 0;
+        const bool lines = i8 && !yt;
         const PanelCfg c8 = lines ? PanelCfg{8, 2, 8, 2} : PanelCfg{8, 2, 12, 2};
         const int64_t n_cg = (ti.n_tiles + 7) / 8;
         const size_t lds = panel_lds_bytes(c8, run_kind, yt, (uint64_t)ti.n_win * 8 * kDenseOp);
@@ -1122,7 +1123,13 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         a.x = x + t0 * x_token_bytes;
         a.y = static_cast<char *>(y) + (yt ? t0 / 16 * a.y_cb * 512 : t0 * w->n_out * out_bytes);
         a.m = std::min(chunk, m - t0);
+        // 16-byte aligned rows: the staged kernel copies them whole; rows that
+        // start at whole words load into registers as they are (buffer loads
+        // take any multiple of 4 bytes and check each word against the
+        // buffer's end), others word by word with a shift
         const bool vec = xt || ((w->k_in % 16 == 0) && ((reinterpret_cast<uintptr_t>(a.x) & 15) == 0));
+        const bool words = xt || ((w->k_in % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.x) & 3) == 0));
+        const RowsAt xl = xt ? RowsAt::kBlocks : words ? RowsAt::kWords : RowsAt::kBytes;
         // Aligned or block-layout rows: the weight-stationary kernel for short
         // reductions (at most kPanelMaxWin windows), with the shape the cost
         // model picks (768x768 at 2048 / 4096 tokens, us, against the kernel
@@ -1146,14 +1153,14 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         const int split_wpw = split_windows_per_wave(ti.n_win);
         const int64_t split_items =
             (a.m + 16 * kSplitSt - 1) / (16 * kSplitSt) * ((ti.n_tiles + kSplitNt - 1) / kSplitNt);
-        if (vec && (force_split || (!*path && split_items <= kSplitAutoItems)) && split_wpw > 0) {
+        if ((force_split || (!*path && split_items <= kSplitAutoItems)) && split_wpw > 0) {
             a.n_cgroups = (ti.n_tiles + kSplitNt - 1) / kSplitNt;
             a.om = nullptr;
             a.ovf = w->dev.ovfd;  // (restored below for the other kernels' chunks)
             a.ovf_bytes = w->dev.ovfd_bytes;
             a.n_items = split_items;
             a.kw = (ti.n_win + split_wpw - 1) / split_wpw;
-            const sl_status sst = launch_split(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, xt, yt, s);
+            const sl_status sst = launch_split(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, xl, yt, s);
             if (sst != SL_OK) return sst;
             set_last_path("split %d,%d kw=%d wpw=%d", kSplitSt, kSplitNt, a.kw, split_wpw);
             a.ovf = w->dev.ovf;
@@ -1162,17 +1169,19 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         }
         const bool force_panel = strcmp(path, "panel") == 0;
         const bool auto_path = !*path;
-        const bool direct = (xt || (yt && vec) || (vec && strcmp(path, "direct") == 0)) &&
+        const bool direct = (xt || (yt && words) || (words && (!vec || strcmp(path, "direct") == 0))) &&
                             !(strcmp(path, "staged") == 0 && !xt && !yt);
-        if (vec && (force_panel || (auto_path && ti.n_win <= kPanelMaxWin))) {
+        // (rows at any byte take it for every reduction whose panel fits: the
+        // staged kernel would store them to LDS byte by byte)
+        if (force_panel || (auto_path && (ti.n_win <= kPanelMaxWin || !words))) {
             PanelCfg pc{};
             size_t lds = 0;
-            sl_status pst = choose_panel_cfg(a, w, run_kind, xt, yt, &pc, &lds);
+            sl_status pst = choose_panel_cfg(a, w, run_kind, xl, yt, &pc, &lds);
             if (pst == SL_OK && !force_panel && xt && kind == SL_EPI_ACC_I32 &&
                 !(w->n_out > w->k_in || a.slice_groups >= 4 * pc.nwv || !one_full_round(direct, a.m, w)))
                 pst = SL_ERR_UNSUPPORTED;
             if (pst == SL_OK) {
-                pst = launch_panel(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, pc, xt, yt, lds, s);
+                pst = launch_panel(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, pc, xl, yt, lds, s);
                 if (pst != SL_OK) return pst;
                 set_last_path("panel %d,%d,%d,%d groups=%d slices=%dx%d lds=%zu", pc.nt, pc.st, pc.nwv, pc.r,
                               a.n_cgroups, a.n_slices, a.slice_groups, lds);

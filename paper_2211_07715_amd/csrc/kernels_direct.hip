@@ -1,5 +1,6 @@
 // The direct-operand kernel of the sparse INT8 linear layer (gfx950): for
-// token rows that are 16-byte aligned (k_in % 16 == 0).
+// token rows in the block layout, or row-major with every row starting at a
+// multiple of 4 bytes.
 //
 // Same method and operand image as the staged kernel (Section "Sparse GEMM
 // operators", Figure 1, Algorithm 1: the stored 4x1 blocks are one operand of

@@ -1,6 +1,6 @@
 // The weight-stationary kernel of the sparse INT8 linear layer (gfx950): for
-// token rows that are 16-byte aligned (k_in % 16 == 0) or in SL_LAYOUT_T16X32,
-// when a channel group's whole weight panel fits in LDS.
+// token rows in either layout and at any alignment, when a channel group's
+// whole weight panel fits in LDS.
 //
 // Same product as the other kernels (Section "Sparse GEMM operators", Figure
 // 1, Algorithm 1: int8 products of the stored weight blocks with the input
@@ -91,9 +91,11 @@ __device__ __forceinline__ void static_for(F &&f)
 
 // R: windows of token rows held in registers (R - 1 of them loading while
 // one is multiplied)
-template <int KIND, int NT, int ST, int NWV, int R, bool XT, bool YT>
+// XL: where the token rows lie (RowsAt).
+template <int KIND, int NT, int ST, int NWV, int R, RowsAt XL, bool YT>
 __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *ep)
 {
+    constexpr bool XT = XL == RowsAt::kBlocks, UA = XL == RowsAt::kBytes;
     using S = PShape<NT, ST, NWV>;
     using L = PLds<KIND, NT, ST, NWV, YT>;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
@@ -147,9 +149,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     // this lane's index word: block-row (lane%16)/4, lane group lane/16
     const int iword = ((lane & 15) >> 2) * 4 + (lane >> 4);
 
-    const int64_t xbytes = XT ? mpad / 16 * a.x_cb * 512 : a.m * a.k;
-    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)a.x, 0, (int)std::min<int64_t>(xbytes, kMaxBufferBytes), kRsrcWord3);
+    const RowSource<XL> src(a);
     // Token rows: lane l of subtile s loads features 32*(l/16) .. +31 of the
     // window for token (l % 16) -- the B operand layout. Tokens past m read
     // zeros (out-of-range offsets) or a padding token of the last block; a
@@ -157,30 +157,15 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     // which meet zero weights.
     auto row_offsets = [&](int64_t t0, uint32_t (&ro)[ST]) {
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            const int64_t r = t0 + s * 16 + (lane & 15);
-            if constexpr (XT)
-                ro[s] = r < mpad ? (uint32_t)((r >> 4) * a.x_cb * 512) + 512u * (uint32_t)(lane >> 4) +
-                                       32u * (uint32_t)(lane & 15)
-                                 : kOob;
-            else
-                ro[s] = r < a.m ? (uint32_t)(r * a.k) + 32u * (uint32_t)(lane >> 4) : kOob;
-        }
+        for (int s = 0; s < ST; ++s) ro[s] = src.offset(a, t0 + s * 16 + (lane & 15), lane >> 4);
     };
-    // (an offset of kOob plus a window's stays past the buffer: such a lane
-    // reads zeros)
-    auto load_rows = [&](i32x8 (&bv)[ST], const uint32_t (&ro)[ST], int w) {
+    auto load_rows = [&](RowPiece<XL> (&bv)[ST], const uint32_t (&ro)[ST], int w) {
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            const uint32_t off = ro[s] + (uint32_t)w * (XT ? 4 * 512 : kWin);
-            const i32x4 lo = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-            const i32x4 hi = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off + 16u, 0, 0));
-            bv[s] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+        for (int s = 0; s < ST; ++s) bv[s] = src.load(ro[s], w);
     };
 
     i32x4 acc[NT][ST];
-    i32x8 bv[R][ST];
+    RowPiece<XL> bv[R][ST];
     static_assert(R >= 2, "at least one window loads while another is multiplied");
 
     // Weight operands in registers, a ring of RS units (one half-window of one
@@ -199,8 +184,12 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     };
     // window u (token rows in ring slot PB, panel bytes cbase; the next
     // window's at nbase)
-    auto multiply = [&](auto pb, uint32_t cbase, uint32_t nbase) {
+    // (ro: the group's row offsets, whose low bits say how its rows lie)
+    auto multiply = [&](auto pb, uint32_t cbase, uint32_t nbase, const uint32_t (&ro)[ST]) {
         constexpr int PB = decltype(pb)::value;
+        i32x8 rows[ST];
+#pragma unroll
+        for (int s = 0; s < ST; ++s) rows[s] = src.aligned(bv[PB][s], ro[s]);
         static_for<NU>([&](auto cc) {
             constexpr int C = decltype(cc)::value;
             constexpr int J = C + LA;
@@ -210,8 +199,8 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
                 read_unit(ring[J % RS], nbase, J - NU);
 #pragma unroll
             for (int s = 0; s < ST; ++s) {
-                const i32x4 b = C < NT ? __builtin_shufflevector(bv[PB][s], bv[PB][s], 0, 1, 2, 3)
-                                           : __builtin_shufflevector(bv[PB][s], bv[PB][s], 4, 5, 6, 7);
+                const i32x4 b = C < NT ? __builtin_shufflevector(rows[s], rows[s], 0, 1, 2, 3)
+                                           : __builtin_shufflevector(rows[s], rows[s], 4, 5, 6, 7);
                 acc[C % NT][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ring[C % RS], b, acc[C % NT][s], 0, 0, 0);
             }
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
@@ -244,7 +233,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
         const int64_t mlim = YT ? mpad : a.m;
         const bool whole = t0 + S::TG <= mlim && (tile0 + NT) * kTileN <= a.n;
         if constexpr (EpiOut<KIND>::kBytes == 1) {
-            if (whole && (YT || (a.n % 16 == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0))) {
+            if (whole) {
                 // int8 codes: a lane holds 4 channels of one token, and four
                 // fragments (a tile of a subtile each) are transposed across
                 // the four lane groups in registers, after which lane group g
@@ -290,7 +279,8 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
                     else
                         p = y8 + (t0 + S0 * 16) * a.n + (tile0 + C0) * kTileN +
                             (uint32_t)((t + (Q ? (g >> 1) * 16 : 0)) * a.n + (Q ? g & 1 : g) * 16);
-                    store_nt(p, i32x4{(int)v[0], (int)v[1], (int)v[2], (int)v[3]});
+                    // (rows of Y start at multiples of 4 bytes)
+                    store_nt_at4(p, i32x4{(int)v[0], (int)v[1], (int)v[2], (int)v[3]});
                 };
                 static_for<NT / 4>([&](auto cq) {
                     static_for<ST>([&](auto sq) {
@@ -447,7 +437,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
                     // the ring reads ahead into this group's next window,
                     // else the next group's first (a stale read past the
                     // last group)
-                    multiply(uc, wbase(u), wbase(u + 1 < a.n_win ? u + 1 : 0));
+                    multiply(uc, wbase(u), wbase(u + 1 < a.n_win ? u + 1 : 0), ro);
                 }
             });
         }
@@ -459,32 +449,32 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     }
 }
 
-template <int KIND, int NT, int ST, int NWV, int R, bool XT, bool YT>
+template <int KIND, int NT, int ST, int NWV, int R, RowsAt XL, bool YT>
 __global__ __launch_bounds__(64 * NWV) void sparse_linear_panel_kernel(LinearArgs a)
 {
-    panel_body<KIND, NT, ST, NWV, R, XT, YT>(a, nullptr);
+    panel_body<KIND, NT, ST, NWV, R, XL, YT>(a, nullptr);
 }
 
-template <int NT, int ST, int NWV, int R, bool XT, bool YT>
+template <int NT, int ST, int NWV, int R, RowsAt XL, bool YT>
 __global__ __launch_bounds__(64 * NWV) void sparse_linear_panel_gelu_kernel(LinearArgs a, GeluArg ep)
 {
-    panel_body<SL_EPI_I8_GELU, NT, ST, NWV, R, XT, YT>(a, &ep);
+    panel_body<SL_EPI_I8_GELU, NT, ST, NWV, R, XL, YT>(a, &ep);
 }
 
-template <int KIND, int NT, int ST, int NWV, int R, bool XT, bool YT>
+template <int KIND, int NT, int ST, int NWV, int R, RowsAt XL, bool YT>
 static const void *panel_fn()
 {
     if constexpr (KIND == SL_EPI_I8_GELU)
-        return reinterpret_cast<const void *>(&sparse_linear_panel_gelu_kernel<NT, ST, NWV, R, XT, YT>);
+        return reinterpret_cast<const void *>(&sparse_linear_panel_gelu_kernel<NT, ST, NWV, R, XL, YT>);
     else
-        return reinterpret_cast<const void *>(&sparse_linear_panel_kernel<KIND, NT, ST, NWV, R, XT, YT>);
+        return reinterpret_cast<const void *>(&sparse_linear_panel_kernel<KIND, NT, ST, NWV, R, XL, YT>);
 }
 
-template <int KIND, int NT, int ST, int NWV, int R, bool XT, bool YT>
+template <int KIND, int NT, int ST, int NWV, int R, RowsAt XL, bool YT>
 static sl_status launch_panel_cfg(const LinearArgs &a, const GeluArg *ep, size_t lds, hipStream_t stream)
 {
     using S = PShape<NT, ST, NWV>;
-    const void *fn = panel_fn<KIND, NT, ST, NWV, R, XT, YT>();
+    const void *fn = panel_fn<KIND, NT, ST, NWV, R, XL, YT>();
     static int raised[kMaxDevices] = {};  // per kernel instance and device: LDS limit raised
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
@@ -498,10 +488,10 @@ static sl_status launch_panel_cfg(const LinearArgs &a, const GeluArg *ep, size_t
     }
     const int64_t nwg = (int64_t)a.n_cgroups * a.n_slices;
     if constexpr (KIND == SL_EPI_I8_GELU)
-        hipLaunchKernelGGL((sparse_linear_panel_gelu_kernel<NT, ST, NWV, R, XT, YT>), dim3((uint32_t)nwg),
+        hipLaunchKernelGGL((sparse_linear_panel_gelu_kernel<NT, ST, NWV, R, XL, YT>), dim3((uint32_t)nwg),
                            dim3(S::NTH), lds, stream, a, *ep);
     else
-        hipLaunchKernelGGL((sparse_linear_panel_kernel<KIND, NT, ST, NWV, R, XT, YT>), dim3((uint32_t)nwg),
+        hipLaunchKernelGGL((sparse_linear_panel_kernel<KIND, NT, ST, NWV, R, XL, YT>), dim3((uint32_t)nwg),
                            dim3(S::NTH), lds, stream, a);
     HIP_TRY(hipGetLastError());
     return SL_OK;
@@ -523,13 +513,14 @@ const PanelCfg kPanelCfgs[kNumPanelCfgs] = {
 #undef SL_PANEL_ENTRY
 };
 
-template <int KIND, bool XT, bool YT>
+template <int KIND, RowsAt XL, bool YT>
 static sl_status launch_panel_kind(const LinearArgs &a, const GeluArg *ep, PanelCfg c, size_t lds,
                                    hipStream_t stream)
 {
 #define SL_PANEL_CASE(NT_, ST_, NWV_, R_)                                \
-    if (c.nt == NT_ && c.st == ST_ && c.nwv == NWV_ && c.r == R_)         \
-        return launch_panel_cfg<KIND, NT_, ST_, NWV_, R_, XT, YT>(a, ep, lds, stream);
+    if constexpr (XL != RowsAt::kBytes || panel_takes_bytes(NT_, ST_, NWV_, R_))            \
+        if (c.nt == NT_ && c.st == ST_ && c.nwv == NWV_ && c.r == R_)                       \
+            return launch_panel_cfg<KIND, NT_, ST_, NWV_, R_, XL, YT>(a, ep, lds, stream);
     SL_PANEL_SHAPES(SL_PANEL_CASE)
 #undef SL_PANEL_CASE
     set_error("internal: unknown weight-stationary workgroup shape");
@@ -566,7 +557,7 @@ sl_status panel_resident(PanelCfg c, size_t lds, int *out)
     int threads = 0;
 #define SL_PANEL_FN(NT_, ST_, NWV_, R_)                                          \
     if (c.nt == NT_ && c.st == ST_ && c.nwv == NWV_ && c.r == R_) {              \
-        fn = panel_fn<SL_EPI_F32, NT_, ST_, NWV_, R_, true, false>();            \
+        fn = panel_fn<SL_EPI_F32, NT_, ST_, NWV_, R_, RowsAt::kBlocks, false>();            \
         threads = PShape<NT_, ST_, NWV_>::NTH;                                   \
     }
     SL_PANEL_SHAPES(SL_PANEL_FN)
@@ -584,33 +575,36 @@ sl_status panel_resident(PanelCfg c, size_t lds, int *out)
     return SL_OK;
 }
 
-template <int KIND, bool XT>
+template <int KIND, RowsAt XL>
 static sl_status launch_panel_y(const LinearArgs &a, const GeluArg *ep, PanelCfg c, bool yt, size_t lds,
                                 hipStream_t stream)
 {
     if constexpr (EpiOut<KIND>::kBytes == 1)
-        if (yt) return launch_panel_kind<KIND, XT, true>(a, ep, c, lds, stream);
-    return launch_panel_kind<KIND, XT, false>(a, ep, c, lds, stream);
+        if (yt) return launch_panel_kind<KIND, XL, true>(a, ep, c, lds, stream);
+    return launch_panel_kind<KIND, XL, false>(a, ep, c, lds, stream);
 }
 
 template <int KIND>
-static sl_status launch_panel_x(const LinearArgs &a, const GeluArg *ep, PanelCfg c, bool xt, bool yt, size_t lds,
+static sl_status launch_panel_x(const LinearArgs &a, const GeluArg *ep, PanelCfg c, RowsAt xl, bool yt, size_t lds,
                                 hipStream_t stream)
 {
-    return xt ? launch_panel_y<KIND, true>(a, ep, c, yt, lds, stream)
-              : launch_panel_y<KIND, false>(a, ep, c, yt, lds, stream);
+    switch (xl) {
+    case RowsAt::kBlocks: return launch_panel_y<KIND, RowsAt::kBlocks>(a, ep, c, yt, lds, stream);
+    case RowsAt::kWords: return launch_panel_y<KIND, RowsAt::kWords>(a, ep, c, yt, lds, stream);
+    default: return launch_panel_y<KIND, RowsAt::kBytes>(a, ep, c, yt, lds, stream);
+    }
 }
 
-sl_status launch_panel(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, PanelCfg c, bool xt, bool yt,
+sl_status launch_panel(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, PanelCfg c, RowsAt xl, bool yt,
                        size_t lds, hipStream_t stream)
 {
     switch (run_kind) {
-    case SL_EPI_ACC_I32: return launch_panel_x<SL_EPI_ACC_I32>(a, nullptr, c, xt, yt, lds, stream);
-    case SL_EPI_F32: return launch_panel_x<SL_EPI_F32>(a, nullptr, c, xt, yt, lds, stream);
-    case SL_EPI_F32_GELU: return launch_panel_x<SL_EPI_F32_GELU>(a, nullptr, c, xt, yt, lds, stream);
-    case SL_EPI_I8: return launch_panel_x<SL_EPI_I8>(a, nullptr, c, xt, yt, lds, stream);
-    case SL_EPI_I8_GELU: return launch_panel_x<SL_EPI_I8_GELU>(a, ep, c, xt, yt, lds, stream);
-    default: return launch_panel_x<kEpiI8GeluErf>(a, nullptr, c, xt, yt, lds, stream);
+    case SL_EPI_ACC_I32: return launch_panel_x<SL_EPI_ACC_I32>(a, nullptr, c, xl, yt, lds, stream);
+    case SL_EPI_F32: return launch_panel_x<SL_EPI_F32>(a, nullptr, c, xl, yt, lds, stream);
+    case SL_EPI_F32_GELU: return launch_panel_x<SL_EPI_F32_GELU>(a, nullptr, c, xl, yt, lds, stream);
+    case SL_EPI_I8: return launch_panel_x<SL_EPI_I8>(a, nullptr, c, xl, yt, lds, stream);
+    case SL_EPI_I8_GELU: return launch_panel_x<SL_EPI_I8_GELU>(a, ep, c, xl, yt, lds, stream);
+    default: return launch_panel_x<kEpiI8GeluErf>(a, nullptr, c, xl, yt, lds, stream);
     }
 }
 

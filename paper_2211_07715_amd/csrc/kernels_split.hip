@@ -26,10 +26,9 @@
 
 namespace sl {
 
-// XT: x in SL_LAYOUT_T16X32 (else row-major, 16-byte aligned rows); YT: y in
-// SL_LAYOUT_T16X32 (int8 kinds). The workgroup has a.kw waves of at most
-// WPW windows each (a.kw * WPW >= n_win).
-template <int KIND, int ST, int NT, int WPW, bool XT, bool YT>
+// XL: where the rows of x lie; YT: y in SL_LAYOUT_T16X32 (int8 kinds). The
+// workgroup has a.kw waves of at most WPW windows each (a.kw * WPW >= n_win).
+template <int KIND, int ST, int NT, int WPW, RowsAt XL, bool YT>
 __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *ep)
 {
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
@@ -60,30 +59,20 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
     // (a.ovf: the overflow image in the main image's layout)
     const __amdgpu_buffer_rsrc_t orc = __builtin_amdgcn_make_buffer_rsrc((void *)a.ovf, 0, (int)a.ovf_bytes,
                                                                          kRsrcWord3);
-    const int64_t xbytes = XT ? (a.m + 15) / 16 * a.x_cb * 512 : a.m * a.k;
-    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)a.x, 0, (int)min<int64_t>(xbytes, kMaxBufferBytes), kRsrcWord3);
+    const RowSource<XL> src(a);
     const uint32_t wstride = (uint32_t)a.n_tiles * kOpBytes;  // main image bytes per window
     // this lane's index word: block-row (lane%16)/4, lane group lane/16
     const int iword = ((lane & 15) >> 2) * 4 + (lane >> 4);
 
     // Token rows: lane l of subtile s loads features 32*(l/16) .. +31 of
-    // the window for token (l % 16) -- the B operand layout (as in the
-    // direct kernel; tokens past m read zeros or a padding token of the last
-    // block, a ragged last window bytes that meet zero weights).
+    // the window for token (l % 16) -- the B operand layout (tokens past m
+    // read zeros or a padding token of the last block, a ragged last window
+    // bytes that meet zero weights).
     uint32_t ro[ST];
 #pragma unroll
-    for (int s = 0; s < ST; ++s) {
-        const int64_t r = t0 + s * 16 + (lane & 15);
-        if constexpr (XT)
-            ro[s] = r < (a.m + 15) / 16 * 16 ? (uint32_t)((r >> 4) * a.x_cb * 512) + 512u * (uint32_t)(lane >> 4) +
-                                                   32u * (uint32_t)(lane & 15)
-                                             : kOob;
-        else
-            ro[s] = r < a.m ? (uint32_t)(r * a.k) + 32u * (uint32_t)(lane >> 4) : kOob;
-    }
+    for (int s = 0; s < ST; ++s) ro[s] = src.offset(a, t0 + s * 16 + (lane & 15), lane >> 4);
 
-    i32x8 bv[WPW][ST];
+    RowPiece<XL> bv[WPW][ST];
     i32x4 av[WPW][NT], ao[WPW][NT];
     int ix[WPW][NT], io[WPW][NT];
 #pragma unroll
@@ -91,13 +80,7 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
         if (j < nw) {
             const uint32_t w = (uint32_t)(wave + j * kw);
 #pragma unroll
-            for (int s = 0; s < ST; ++s) {
-                const uint32_t off = ro[s] + w * (XT ? 4 * 512 : kWin);
-                const i32x4 lo = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-                const i32x4 hi =
-                    __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off + 16u, 0, 0));
-                bv[j][s] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            }
+            for (int s = 0; s < ST; ++s) bv[j][s] = src.load(ro[s], (int)w);
 #pragma unroll
             for (int c = 0; c < NT; ++c) {
                 const uint32_t base = c < ntl ? (uint32_t)(tile0 + c) * (uint32_t)kOpBytes : kOob;
@@ -144,16 +127,19 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
 #pragma unroll
     for (int j = 0; j < WPW; ++j) {
         if (j < nw) {
+            i32x8 rows[ST];
+#pragma unroll
+            for (int s = 0; s < ST; ++s) rows[s] = src.aligned(bv[j][s], ro[s]);
 #pragma unroll
             for (int c = 0; c < NT; ++c)
 #pragma unroll
                 for (int s = 0; s < ST; ++s)
-                    acc[c][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(av[j][c], bv[j][s], acc[c][s], ix[j][c], 0, 0);
+                    acc[c][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(av[j][c], rows[s], acc[c][s], ix[j][c], 0, 0);
 #pragma unroll
             for (int c = 0; c < NT; ++c)
 #pragma unroll
                 for (int s = 0; s < ST; ++s)
-                    acc[c][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(ao[j][c], bv[j][s], acc[c][s], io[j][c], 0, 0);
+                    acc[c][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(ao[j][c], rows[s], acc[c][s], io[j][c], 0, 0);
         }
     }
 #pragma unroll
@@ -186,53 +172,57 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
     }
 }
 
-template <int KIND, int ST, int NT, int WPW, bool XT, bool YT>
+template <int KIND, int ST, int NT, int WPW, RowsAt XL, bool YT>
 __global__ __launch_bounds__(64 * kSplitMaxWaves) void sparse_linear_split_kernel(LinearArgs a)
 {
-    split_body<KIND, ST, NT, WPW, XT, YT>(a, nullptr);
+    split_body<KIND, ST, NT, WPW, XL, YT>(a, nullptr);
 }
 
-template <int ST, int NT, int WPW, bool XT, bool YT>
+template <int ST, int NT, int WPW, RowsAt XL, bool YT>
 __global__ __launch_bounds__(64 * kSplitMaxWaves) void sparse_linear_split_gelu_kernel(LinearArgs a, GeluArg ep)
 {
-    split_body<SL_EPI_I8_GELU, ST, NT, WPW, XT, YT>(a, &ep);
+    split_body<SL_EPI_I8_GELU, ST, NT, WPW, XL, YT>(a, &ep);
 }
 
-template <int KIND, int WPW, bool XT, bool YT>
+template <int KIND, int WPW, RowsAt XL, bool YT>
 static sl_status launch_split_wpw(const LinearArgs &a, const GeluArg *ep, hipStream_t stream)
 {
     constexpr int ST = kSplitSt, NT = kSplitNt;
     const size_t lds = (size_t)a.kw * NT * ST * 1024 + (KIND == SL_EPI_I8_GELU ? kGeluLds : 0);
     const dim3 grid((uint32_t)a.n_items), block((uint32_t)(64 * a.kw));
     if constexpr (KIND == SL_EPI_I8_GELU)
-        hipLaunchKernelGGL((sparse_linear_split_gelu_kernel<ST, NT, WPW, XT, YT>), grid, block, lds, stream, a, *ep);
+        hipLaunchKernelGGL((sparse_linear_split_gelu_kernel<ST, NT, WPW, XL, YT>), grid, block, lds, stream, a, *ep);
     else
-        hipLaunchKernelGGL((sparse_linear_split_kernel<KIND, ST, NT, WPW, XT, YT>), grid, block, lds, stream, a);
+        hipLaunchKernelGGL((sparse_linear_split_kernel<KIND, ST, NT, WPW, XL, YT>), grid, block, lds, stream, a);
     HIP_TRY(hipGetLastError());
     return SL_OK;
 }
 
-template <int KIND, bool XT, bool YT>
+template <int KIND, RowsAt XL, bool YT>
 static sl_status launch_split_kind(const LinearArgs &a, const GeluArg *ep, int wpw, hipStream_t stream)
 {
     static_assert(kSplitWin == 2, "one instance per windows-per-wave count");
-    if (wpw == 1) return launch_split_wpw<KIND, 1, XT, YT>(a, ep, stream);
-    return launch_split_wpw<KIND, 2, XT, YT>(a, ep, stream);
+    if (wpw == 1) return launch_split_wpw<KIND, 1, XL, YT>(a, ep, stream);
+    return launch_split_wpw<KIND, 2, XL, YT>(a, ep, stream);
 }
 
-template <int KIND, bool XT>
+template <int KIND, RowsAt XL>
 static sl_status launch_split_y(const LinearArgs &a, const GeluArg *ep, int wpw, bool yt, hipStream_t stream)
 {
     if constexpr (EpiOut<KIND>::kBytes == 1)
-        if (yt) return launch_split_kind<KIND, XT, true>(a, ep, wpw, stream);
-    return launch_split_kind<KIND, XT, false>(a, ep, wpw, stream);
+        if (yt) return launch_split_kind<KIND, XL, true>(a, ep, wpw, stream);
+    return launch_split_kind<KIND, XL, false>(a, ep, wpw, stream);
 }
 
 template <int KIND>
-static sl_status launch_split_x(const LinearArgs &a, const GeluArg *ep, int wpw, bool xt, bool yt,
+static sl_status launch_split_x(const LinearArgs &a, const GeluArg *ep, int wpw, RowsAt xl, bool yt,
                                 hipStream_t stream)
 {
-    return xt ? launch_split_y<KIND, true>(a, ep, wpw, yt, stream) : launch_split_y<KIND, false>(a, ep, wpw, yt, stream);
+    switch (xl) {
+    case RowsAt::kBlocks: return launch_split_y<KIND, RowsAt::kBlocks>(a, ep, wpw, yt, stream);
+    case RowsAt::kWords: return launch_split_y<KIND, RowsAt::kWords>(a, ep, wpw, yt, stream);
+    default: return launch_split_y<KIND, RowsAt::kBytes>(a, ep, wpw, yt, stream);
+    }
 }
 
 int split_windows_per_wave(int32_t n_win)
@@ -242,7 +232,7 @@ int split_windows_per_wave(int32_t n_win)
     return 0;
 }
 
-sl_status launch_split(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, bool xt, bool yt,
+sl_status launch_split(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, RowsAt xl, bool yt,
                        hipStream_t stream)
 {
     const int wpw = split_windows_per_wave(a.n_win);
@@ -253,12 +243,12 @@ sl_status launch_split(const LinearArgs &a, const GeluArg *ep, int32_t run_kind,
     }
     if (a.n_items == 0) return SL_OK;
     switch (run_kind) {
-    case SL_EPI_ACC_I32: return launch_split_x<SL_EPI_ACC_I32>(a, nullptr, wpw, xt, yt, stream);
-    case SL_EPI_F32: return launch_split_x<SL_EPI_F32>(a, nullptr, wpw, xt, yt, stream);
-    case SL_EPI_F32_GELU: return launch_split_x<SL_EPI_F32_GELU>(a, nullptr, wpw, xt, yt, stream);
-    case SL_EPI_I8: return launch_split_x<SL_EPI_I8>(a, nullptr, wpw, xt, yt, stream);
-    case SL_EPI_I8_GELU: return launch_split_x<SL_EPI_I8_GELU>(a, ep, wpw, xt, yt, stream);
-    default: return launch_split_x<kEpiI8GeluErf>(a, nullptr, wpw, xt, yt, stream);
+    case SL_EPI_ACC_I32: return launch_split_x<SL_EPI_ACC_I32>(a, nullptr, wpw, xl, yt, stream);
+    case SL_EPI_F32: return launch_split_x<SL_EPI_F32>(a, nullptr, wpw, xl, yt, stream);
+    case SL_EPI_F32_GELU: return launch_split_x<SL_EPI_F32_GELU>(a, nullptr, wpw, xl, yt, stream);
+    case SL_EPI_I8: return launch_split_x<SL_EPI_I8>(a, nullptr, wpw, xl, yt, stream);
+    case SL_EPI_I8_GELU: return launch_split_x<SL_EPI_I8_GELU>(a, ep, wpw, xl, yt, stream);
+    default: return launch_split_x<kEpiI8GeluErf>(a, nullptr, wpw, xl, yt, stream);
     }
 }
 

@@ -32,6 +32,14 @@ __device__ __forceinline__ void store_nt(void *p, V v)
     }
 }
 
+// A 16-byte output store at a multiple of 4 bytes (which the hardware takes as
+// one access).
+typedef int i32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_nt_at4(void *p, i32x4 v)
+{
+    __builtin_nontemporal_store((i32x4_at4)v, reinterpret_cast<i32x4_at4 *>(p));
+}
+
 constexpr int kXcds = 8;  // accelerator complex dies, each with its own L2
 constexpr int kMaxDevices = 64;
 // Buffer-load offset past any buffer this library reads (all < 2 GiB): such
@@ -90,6 +98,76 @@ __device__ __forceinline__ int64_t t16x32_offset(int64_t t, int32_t c, int32_t c
 {
     return ((t >> 4) * cb + (c >> 5)) * 512 + (t & 15) * 32 + (c & 31);
 }
+
+// Where the token rows of X lie, for the kernels that load B operands (32
+// features of one token a lane) straight into registers.
+enum class RowsAt {
+    kBlocks,  // SL_LAYOUT_T16X32
+    kWords,   // row-major, every row starting at a multiple of 4 bytes: buffer loads need no more
+    kBytes,   // row-major, anywhere
+};
+
+// A lane's piece of one window as loaded. Rows at any byte are read as the 9
+// aligned words that hold the 32 bytes (no word without a byte of X is read,
+// so no access leaves X's pages) and shifted into place when they are used.
+template <RowsAt XL>
+struct RowPiece {
+    i32x8 v;
+};
+template <>
+struct RowPiece<RowsAt::kBytes> {
+    i32x8 v;
+    int last;
+};
+
+template <RowsAt XL>
+struct RowSource {
+    static constexpr bool XT = XL == RowsAt::kBlocks;
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t mis;   // bytes of X's first word before X
+    int64_t mpad;
+
+    __device__ __forceinline__ explicit RowSource(const LinearArgs &a)
+    {
+        mpad = (a.m + 15) / 16 * 16;
+        mis = XL == RowsAt::kBytes ? (uint32_t)(reinterpret_cast<uintptr_t>(a.x) & 3) : 0u;
+        const int64_t bytes = XT ? mpad / 16 * a.x_cb * 512
+                                 : (XL == RowsAt::kBytes ? (a.m * a.k + mis + 3) / 4 * 4 : a.m * a.k);
+        rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.x - mis), 0, (int)bytes, kRsrcWord3);
+    }
+    // byte offset of 32-feature group g (0..3) of window 0 of token r; past
+    // the buffer for tokens past the last (in the block layout, block)
+    __device__ __forceinline__ uint32_t offset(const LinearArgs &a, int64_t r, int g) const
+    {
+        if constexpr (XT)
+            return r < mpad ? (uint32_t)((r >> 4) * a.x_cb * 512) + 512u * (uint32_t)g + 32u * (uint32_t)(r & 15) : kOob;
+        else
+            return r < a.m ? mis + (uint32_t)(r * a.k) + 32u * (uint32_t)g : kOob;
+    }
+    // (an offset of kOob plus a window's stays past the buffer: zeros)
+    __device__ __forceinline__ RowPiece<XL> load(uint32_t off, int w) const
+    {
+        const uint32_t o = (XL == RowsAt::kBytes ? off & ~3u : off) + (uint32_t)w * (XT ? 4 * 512 : kWin);
+        const i32x4 lo = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0));
+        const i32x4 hi = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o + 16u, 0, 0));
+        RowPiece<XL> p;
+        p.v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        if constexpr (XL == RowsAt::kBytes) p.last = (int)__builtin_amdgcn_raw_buffer_load_b32(rsrc, o + 32u, 0, 0);
+        return p;
+    }
+    __device__ __forceinline__ i32x8 aligned(const RowPiece<XL> &p, uint32_t off) const
+    {
+        if constexpr (XL == RowsAt::kBytes) {
+            i32x8 r;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                r[i] = (int)__builtin_amdgcn_alignbyte((uint32_t)(i < 7 ? p.v[i < 7 ? i + 1 : 7] : p.last), (uint32_t)p.v[i], off);
+            return r;
+        } else {
+            return p.v;
+        }
+    }
+};
 
 // internal kind: GELU + requantisation evaluated with erf (no usable table)
 constexpr int kEpiI8GeluErf = 5;
@@ -369,7 +447,7 @@ struct ItemIter {
 
 // Workgroup shapes of the direct-operand kernel (kernels_direct.hip): WM
 // compute waves of ST 16-token subtiles x NT 16-channel tiles, D windows in
-// flight. Only for 16-byte aligned token rows (k_in % 16 == 0).
+// flight. Rows in the block layout or at whole words.
 struct DirectCfg {
     int st, nt, wm, d;
     int tm() const { return 16 * st * wm; }
@@ -393,7 +471,7 @@ constexpr int kSplitWin = 2;
 constexpr int kSplitMaxWaves = 16;
 constexpr int64_t kSplitAutoItems = 1280;  // automatic choice up to this many work items
 int split_windows_per_wave(int32_t n_win);
-sl_status launch_split(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, bool xt, bool yt,
+sl_status launch_split(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, RowsAt xl, bool yt,
                        hipStream_t stream);
 
 // Workgroup shapes of the weight-stationary kernel (kernels_panel.hip): NWV
@@ -408,8 +486,14 @@ constexpr int kNumPanelCfgs = 7;
 extern const PanelCfg kPanelCfgs[kNumPanelCfgs];
 // LDS bytes of a panel kernel launch whose panel takes `panel` bytes
 size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, bool yt, uint64_t panel);
-sl_status launch_panel(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, PanelCfg c, bool xt, bool yt,
+sl_status launch_panel(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, PanelCfg c, RowsAt xl, bool yt,
                        size_t lds, hipStream_t stream);
+// The shapes that also come for RowsAt::kBytes: the widest and the narrowest
+// channel groups (reductions up to 1280 and 4992 columns) and one between.
+constexpr bool panel_takes_bytes(int nt, int st, int nwv, int r)
+{
+    return (nt == 8 && nwv == 8) || (nt == 4 && st == 2) || (nt == 2 && st == 2);
+}
 // resident workgroups of a panel-kernel shape for `lds` bytes of LDS (all kinds and layouts of a
 // shape share one register budget; the SL_EPI_F32 row-major instance stands for them)
 sl_status panel_resident(PanelCfg c, size_t lds, int *out);

@@ -1,5 +1,5 @@
 """GPU parity of the weight-stationary kernel's 8-tile shapes and of its int8
-stores (16 bytes a lane where rows allow it, else 4), through the C ABI: every
+stores (16 bytes a lane at any multiple of 4), through the C ABI: every
 epilogue kind and layout pairing at the edges of its tiles -- a ragged last
 channel tile, channel group, token group and window, row widths that are no
 multiple of 16, an output that is only 4-byte aligned, one window and several
@@ -45,10 +45,10 @@ def test_wide_shapes(hip, monkeypatch, shape, m, n, k):
     pw.free()
 
 
-# (n, k, m, kind, block layouts): int8 rows of whole 16 bytes, int8 rows that
-# are not, and blocks whose 6-tile groups leave a remainder
+# (n, k, m, kind, block layouts): int8 and fp32 rows, and blocks whose 6-tile
+# groups leave a remainder or not
 @pytest.mark.parametrize("n,k,m,kind,blocks,want", [
-    (2304, 768, 4096, 3, False, "panel 8,2,8,2"), (2308, 768, 4096, 3, False, "panel 6,2"),
+    (2304, 768, 4096, 3, False, "panel 8,2,8,2"), (2308, 768, 4096, 1, False, "panel 6,2"),
     (4096, 1024, 8192, 3, True, "panel 8,2,12,2"), (3072, 768, 4096, 3, True, "panel 6,2,12,2"),
     (768, 768, 4096, 3, True, "panel"), (768, 768, 4096, 1, False, "panel")])
 def test_wide_choice(hip, monkeypatch, n, k, m, kind, blocks, want):
