@@ -685,24 +685,9 @@ sl_status upload_image(sl_packed_weight *w)
         for (uint32_t e = w->row_ptr[g]; e < w->row_ptr[g + 1]; ++e) {
             const int32_t c = w->col[e] % kWin;
             int8_t *const op = dense.data() + ((size_t)(w->col[e] / kWin) * ti.n_tiles + g / 4) * kDenseOp +
-                               (c % 32 / 16) * 1024 + (16 * (c / 32) + 4 * (g % 4)) * 16 + c % 16;
+                               (c / 64) * 1024 + (16 * (c % 64 / 16) + 4 * (g % 4)) * 16 + c % 16;
             for (int r = 0; r < 4; ++r) op[16 * r] = w->vals[4 * (size_t)e + r];
         }
-    // the dense overflow image of the split-reduction and direct kernels: a
-    // tile's overflow operand of a window at the offset of its main operand,
-    // zeros where it has none (the same size as the main image, which is
-    // known to fit one buffer)
-    std::vector<int8_t> odense(ti.main.size(), 0);
-    {
-        const size_t pstride = (size_t)ti.n_tiles + 1;
-        for (int wi = 0; wi < ti.n_win; ++wi)
-            for (int t = 0; t < ti.n_tiles; ++t) {
-                const uint32_t *pp = ti.ovf_ptr.data() + (size_t)wi * pstride + t;
-                if (pp[1] > pp[0])
-                    memcpy(odense.data() + ((size_t)wi * ti.n_tiles + t) * kOpBytes,
-                           ti.ovf.data() + (size_t)pp[0] * kOpBytes, kOpBytes);
-            }
-    }
     const size_t b_main = std::max<size_t>(ti.main.size(), 16);
     const size_t b_ovf = std::max<size_t>(ti.ovf.size(), 16);
     const size_t b_vec = (size_t)w->n_out * sizeof(float);
@@ -718,8 +703,6 @@ sl_status upload_image(sl_packed_weight *w)
     }
     const size_t o_dense = o_end;
     o_end = align256(o_end + dense.size());
-    const size_t o_ovfd = o_end;
-    o_end = align256(o_end + b_main);
     const size_t total = o_end;
     void *base = nullptr;
     hipError_t e = hipMalloc(&base, total);
@@ -744,9 +727,6 @@ sl_status upload_image(sl_packed_weight *w)
     HIP_TRY(hipMemcpy(p + o_dense, dense.data(), dense.size(), hipMemcpyHostToDevice));
     w->dev.dense = reinterpret_cast<const int8_t *>(p + o_dense);
     w->dev.dense_bytes = (uint32_t)dense.size();
-    if (!odense.empty()) HIP_TRY(hipMemcpy(p + o_ovfd, odense.data(), odense.size(), hipMemcpyHostToDevice));
-    w->dev.ovfd = reinterpret_cast<const int8_t *>(p + o_ovfd);
-    w->dev.ovfd_bytes = (uint32_t)odense.size();
     w->dev.main = reinterpret_cast<const int8_t *>(p + o_main);
     w->dev.ovf = reinterpret_cast<const int8_t *>(p + o_ovf);
     w->dev.ovf_ptr = nullptr;
@@ -942,6 +922,40 @@ static bool one_full_round(bool direct, int64_t m, const sl_packed_weight *w)
     }
     const int64_t items = (m + tm - 1) / tm * ((w->tiles.n_tiles + nt - 1) / nt);
     return items <= n_cu && items * 5 >= (int64_t)n_cu * 4;
+}
+
+// Channel tiles of the tile kernel's workgroups for a launch, or 0 where
+// another kernel runs. Of 6 and 8 tiles the one whose workgroups need less
+// time by rounds of the CUs times the operand bytes of a window (128 tokens
+// and 16 channels a tile; 4096 tokens, fp32 rows, us: 768x3072 6 tiles 16.4, 8
+// tiles 17.7, 1024x4096 34.5 and 22.8).
+//  * From row-major X, and for int8 rows of Y: where its 6-tile workgroups
+//    would fill over half of the CUs (768x3072, us, against the staged or
+//    direct kernel: 2900 tokens 22.7 -> 15.4, 4096 18.3 -> 16.4, 49152 176 ->
+//    148, int8 20.2 -> 15.5 and 187 -> 141, int8 from blocks 156 -> 139; at
+//    2048, 128 workgroups, 14.1 against 14.6).
+//  * From block-layout X the direct kernel loads half the operands past LDS
+//    and is faster per round: only where the 8-tile workgroups take less than
+//    0.83 of its time by that count (1024x4096 at 4096 / 49152 tokens 30.1 ->
+//    23.0 / 262 -> 250; 768x3072 at 49152, 0.86 by that count: 141 and 148).
+static int choose_tile_nt(const char *path, bool auto_path, bool xt, bool yt, int64_t out_bytes, int64_t m,
+                          const sl_packed_weight *w)
+{
+    const bool forced = strcmp(path, "tile") == 0;
+    if (!forced && !(auto_path && w->tiles.n_win > kPanelMaxWin)) return 0;
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
+        return forced ? 6 : 0;
+    const auto items = [&](int nt) {
+        return (m + kTileTokens - 1) / kTileTokens * ((w->tiles.n_tiles + nt - 1) / nt);
+    };
+    const auto time = [&](int nt) { return (items(nt) + n_cu - 1) / n_cu * (kTileTokens + 16 * nt); };
+    if (forced && env_cfg().tile[0] > 0) return env_cfg().tile[0] == 8 ? 8 : 6;
+    const int nt = time(8) < time(6) ? 8 : 6;
+    if (forced || ((!xt || (out_bytes == 1 && !yt)) && items(6) * 2 > n_cu)) return nt;
+    // (the direct kernel's items are 128 tokens x 6 tiles too)
+    return xt && time(8) * 100 < time(6) * 83 ? 8 : 0;
 }
 
 // Token slices of a weight-stationary launch: `want` per channel group.
@@ -1156,15 +1170,11 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         if ((force_split || (!*path && split_items <= kSplitAutoItems)) && split_wpw > 0) {
             a.n_cgroups = (ti.n_tiles + kSplitNt - 1) / kSplitNt;
             a.om = nullptr;
-            a.ovf = w->dev.ovfd;  // (restored below for the other kernels' chunks)
-            a.ovf_bytes = w->dev.ovfd_bytes;
             a.n_items = split_items;
             a.kw = (ti.n_win + split_wpw - 1) / split_wpw;
             const sl_status sst = launch_split(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, xl, yt, s);
             if (sst != SL_OK) return sst;
             set_last_path("split %d,%d kw=%d wpw=%d", kSplitSt, kSplitNt, a.kw, split_wpw);
-            a.ovf = w->dev.ovf;
-            a.ovf_bytes = (uint32_t)ti.ovf.size();
             continue;
         }
         const bool force_panel = strcmp(path, "panel") == 0;
@@ -1188,6 +1198,17 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
                 continue;
             }
             if (pst != SL_ERR_UNSUPPORTED) return pst;
+        }
+        // Long reductions (and SL_PATH=tile) over enough tokens: the tile kernel.
+        const int tile_nt = vec ? choose_tile_nt(path, auto_path, xt, yt, out_bytes, a.m, w) : 0;
+        if (tile_nt) {
+            a.n_cgroups = (ti.n_tiles + tile_nt - 1) / tile_nt;
+            a.n_items = (a.m + kTileTokens - 1) / kTileTokens * a.n_cgroups;
+            const sl_status tst =
+                launch_tile(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, tile_nt, xt, yt, s);
+            if (tst != SL_OK) return tst;
+            set_last_path("tile %d,%d", kTileTokens, tile_nt);
+            continue;
         }
         TileCfg cfg{};
         DirectCfg dcfg{};
@@ -1217,11 +1238,7 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         }
         sl_status st;
         if (direct) {
-            a.ovf = w->dev.ovfd;  // (restored below for the other kernels' chunks)
-            a.ovf_bytes = w->dev.ovfd_bytes;
             st = launch_direct(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, dcfg, xt, yt, s);
-            a.ovf = w->dev.ovf;
-            a.ovf_bytes = (uint32_t)ti.ovf.size();
             set_last_path("direct %d,%d,%d,%d", dcfg.st, dcfg.nt, dcfg.wm, dcfg.d);
         } else {
             set_last_path("staged %d,%d,%d,%d,%d", cfg.st, cfg.ct, cfg.wm, cfg.wn, cfg.d);

@@ -2,26 +2,26 @@
 // token rows in the block layout, or row-major with every row starting at a
 // multiple of 4 bytes.
 //
-// Same method and operand image as the staged kernel (Section "Sparse GEMM
-// operators", Figure 1, Algorithm 1: the stored 4x1 blocks are one operand of
-// the 4:2-sparse int8 matrix instruction, the input columns the weight's mask
-// names are selected by the instruction's column indices, int32 accumulation,
-// one fused epilogue per output). What differs is where the dense operand
-// comes from. Each compute wave owns ST 16-token subtiles and all NT channel
-// tiles of the workgroup, so no two waves use the same token rows: a wave
-// loads its B operands (32 bytes of one token row per lane) straight from
-// memory into registers, two windows ahead, and only the weight operands
-// pass through LDS, where all compute waves share them. That halves the LDS
-// traffic of a window and leaves LDS bandwidth to the weight operands.
+// Same product as the other kernels (Section "Sparse GEMM operators", Figure
+// 1, Algorithm 1), from the dense operand image (kernels_panel.hip says why).
+// Each compute wave owns ST 16-token subtiles and all NT channel tiles of the
+// workgroup, so no two waves use the same token rows: a wave loads its B
+// operands straight from memory into registers, a window ahead, and only the
+// weight operands pass through LDS, where all compute waves share them. That
+// leaves LDS bandwidth to the weight operands.
 //
 // Copy waves stream each window's weight operands into a ring of D LDS
-// buffers: the NT main operands and the NT overflow operand slots, both read
-// at the same offsets from the main image and from the dense overflow image
-// (zeros where a tile has no overflow operand). No table lies on the way to
-// a copy's address, so the first element's copies start at kernel entry, and
-// every window takes the same number of copies, which keeps the waits that
-// count them constant. Work items (token tile x channel group) are spread
-// over a persistent grid.
+// buffers; no table lies on the way to a copy's address, so the first
+// element's copies start at kernel entry, and every window takes the same
+// number of copies, which keeps the waits that count them constant. Work items
+// (token tile x channel group) are spread over a persistent grid.
+//
+// What bounds it: bytes from L2 a CU (29 KB a window for 24 matrix instructions
+// a wave) and each wave's order of loads, LDS reads and matrix instructions,
+// one wave a SIMD. Two compute waves a SIMD, each over half of every window
+// with the sums met in LDS, were slower (FFN2 at 4096 tokens 13.6 -> 16.6 us).
+// 4:2-sparse operands -> dense, us, FFN2 768x3072 in blocks: 1024 tokens 10.5
+// -> 8.7, 2048 11.0 -> 8.8, 4096 14.3 -> 13.4, 49152 143 -> 141.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,30 +33,26 @@ namespace sl {
 
 // Workgroup shape: WM compute waves along the tokens, each with ST 16-token
 // subtiles x all NT 16-channel tiles; as many copy waves; D windows in flight.
-// One window's buffer: NT main operands, then NT overflow operand slots (one
-// per tile, zeros where the tile has none); each region is padded to whole
-// 64-lane copies per copy wave.
+// One window's buffer: NT pairs of operands.
 template <int ST, int NT, int WM, int D>
 struct DShape {
     static constexpr int NW = WM;
-    static constexpr int NTH = 64 * NW;                          // lanes of the compute (and of the copy) waves
-    static constexpr int NTHG = 2 * NTH;                         // threads per workgroup
-    static constexpr int TM = 16 * ST * WM;                      // tokens per work item
-    static constexpr int CA = (NT * kOpPieces + NTH - 1) / NTH;  // copies per copy wave per region
-    static constexpr int AB = CA * NTH * 16;
-    static constexpr int COPIES = 2 * CA;  // per copy wave per window: main, overflow
-    static constexpr int BUF = 2 * AB;
+    static constexpr int NTH = 64 * NW;                // lanes of the compute (and of the copy) waves
+    static constexpr int NTHG = 2 * NTH;               // threads per workgroup
+    static constexpr int TM = 16 * ST * WM;            // tokens per work item
+    static constexpr int COPIES = 2 * NT / NW;         // 1024-byte copies per copy wave per window
+    static constexpr int BUF = NT * kDenseOp;
     static constexpr int LDS = D * BUF;
-    static constexpr int VEC = 2 * NT * kTileN * 4;  // per compute wave: weight scales, then biases
+    static constexpr int VEC = 2 * NT * kTileN * 4;    // per compute wave: weight scales, then biases
     // per compute wave: 16 token rows of 32 four-byte outputs (two tiles),
     // padded to 36 words so that neither the writes nor the reads of the
     // transpose meet a bank twice in one pass
     static constexpr int TRW = 36;
     static constexpr int TR = 16 * TRW * 4;
-    static_assert(NT <= 32, "an overflow mask has 32 bits");
+    static_assert(2 * NT % NW == 0, "every copy wave issues the same number of copies");
 };
 
-// XT: x in SL_LAYOUT_T16X32 (else row-major, 16-byte aligned rows); YT: y in
+// XT: x in SL_LAYOUT_T16X32 (else row-major rows at whole words); YT: y in
 // SL_LAYOUT_T16X32 (int8 kinds).
 template <int KIND, int ST, int NT, int WM, int D, bool XT, bool YT>
 __device__ __forceinline__ void direct_body(const LinearArgs &a, const GeluArg *ep)
@@ -104,32 +100,20 @@ __device__ __forceinline__ void direct_body(const LinearArgs &a, const GeluArg *
     static_assert((D - 1) * S::COPIES < 64, "outstanding copies must fit the 6-bit vector-memory counter");
 
     if (copier) {
-        const __amdgpu_buffer_rsrc_t mr =
-            __builtin_amdgcn_make_buffer_rsrc((void *)a.main, 0, (int)a.main_bytes, kRsrcWord3);
-        const __amdgpu_buffer_rsrc_t orc =
-            __builtin_amdgcn_make_buffer_rsrc((void *)a.ovf, 0, (int)a.ovf_bytes, kRsrcWord3);
-        const uint32_t wstride = (uint32_t)a.n_tiles * kOpBytes;  // main image bytes per window
-        // this lane's piece (tile, 16-byte piece) of each operand-region copy
-        int32_t atile[S::CA], apiece16[S::CA];
-#pragma unroll
-        for (int i = 0; i < S::CA; ++i) {
-            const int piece = (i * S::NW + pw) * 64 + lane;
-            atile[i] = piece / kOpPieces;
-            apiece16[i] = (piece - atile[i] * kOpPieces) * 16;
-        }
+        // (tiles past the last one copy the next window's operands, or zeros
+        // past the image: their channels are never stored)
+        const __amdgpu_buffer_rsrc_t wr =
+            __builtin_amdgcn_make_buffer_rsrc((void *)a.dense, 0, (int)a.dense_bytes, kRsrcWord3);
+        const uint32_t wstride = (uint32_t)a.n_tiles * kDenseOp;  // image bytes per window
 
         // element cursor (item ic, the kc-th of this workgroup; window wc);
         // past the last element it repeats the last one
         ItemIter ic = first;
         int kc = 0, wc = 0;
         auto cur_w = [&]() { return phys(ic, kc < n_my ? wc : a.n_win - 1); };
-        uint32_t aoff[S::CA];
+        uint32_t aoff = 0;
         auto item_offsets = [&]() {
-            const int32_t tile0 = ic.cg * NT;
-            const int32_t ntl = min(NT, a.n_tiles - tile0);
-#pragma unroll
-            for (int i = 0; i < S::CA; ++i)
-                aoff[i] = atile[i] < ntl ? (uint32_t)((tile0 + atile[i]) * kOpBytes + apiece16[i]) : kOob;
+            aoff = (uint32_t)(ic.cg * NT) * kDenseOp + (uint32_t)(pw * 1024 + lane * 16);
         };
         auto advance = [&]() {
             if (++wc == a.n_win) {
@@ -143,16 +127,11 @@ __device__ __forceinline__ void direct_body(const LinearArgs &a, const GeluArg *
         item_offsets();
 
         // Copy k (0 <= k < COPIES) of the cursor's element (physical window
-        // w) into ring buffer bi: main operands, then overflow slots.
+        // w) into ring buffer bi.
         auto copy = [&](int k, int w, int bi) {
-            int8_t *b = smem + bi * S::BUF;
-            const uint32_t wo = (uint32_t)w * wstride;
-            if (k < S::CA)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(mr, (lds_void *)(b + (k * S::NW + pw) * 1024), 16, aoff[k],
-                                                         wo, 0, 0);
-            else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(orc, (lds_void *)(b + S::AB + ((k - S::CA) * S::NW + pw) * 1024),
-                                                         16, aoff[k - S::CA], wo, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                wr, (lds_void *)(smem + bi * S::BUF + (k * S::NW + pw) * 1024), 16,
+                aoff + (uint32_t)w * wstride + (uint32_t)(k * S::NW * 1024), 0, 0, 0);
         };
 
         // Prologue: the copies of elements 0..D-1, element by element; a bare
@@ -202,63 +181,41 @@ __device__ __forceinline__ void direct_body(const LinearArgs &a, const GeluArg *
 
     // ---- compute waves
     const int wm = wave;
-    // this lane's index word: block-row (lane%16)/4, lane group lane/16
-    const int iword = ((lane & 15) >> 2) * 4 + (lane >> 4);
 
-    // Token rows: lane l of subtile s loads features 32*(l/16) .. +31 of its
-    // window for token (l % 16) -- the B operand layout. Row-major: 32 bytes
-    // of the token's row; block layout: 32 bytes of the token's row in block
-    // 4w + l/16, so each group of 4 lanes reads one cache line. Tokens past m
-    // read zeros (out-of-range offsets) or a padding token of the last block;
-    // a ragged last window reads bytes past the row (or zeros past the
+    // Token rows: lane l of subtile s loads features 16*(l/16) .. +15 of each
+    // half of its window for token (l % 16) -- the B operand layout. Tokens
+    // past m read zeros (out-of-range offsets) or a padding token of the last
+    // block; a ragged last window reads bytes past the row (or zeros past the
     // buffer), which meet zero weights.
-    const int64_t xbytes = XT ? (a.m + 15) / 16 * a.x_cb * 512 : a.m * a.k;
-    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)a.x, 0, (int)min<int64_t>(xbytes, kMaxBufferBytes), kRsrcWord3);
+    using Rows = RowSource<XT ? RowsAt::kBlocks : RowsAt::kWords>;
+    using Piece = RowPiece<XT ? RowsAt::kBlocks : RowsAt::kWords>;
+    const Rows src(a);
     auto row_offsets = [&](const ItemIter &it, uint32_t (&ro)[ST]) {
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            const int64_t r = (int64_t)it.mt * S::TM + wm * ST * 16 + s * 16 + (lane & 15);
-            if constexpr (XT)
-                ro[s] = r < (a.m + 15) / 16 * 16 ? (uint32_t)((r >> 4) * a.x_cb * 512) + 512u * (uint32_t)(lane >> 4) +
-                                                       32u * (uint32_t)(lane & 15)
-                                                 : kOob;
-            else
-                ro[s] = r < a.m ? (uint32_t)(r * a.k) + 32u * (uint32_t)(lane >> 4) : kOob;
-        }
+        for (int s = 0; s < ST; ++s)
+            ro[s] = src.offset(a, (int64_t)it.mt * S::TM + wm * ST * 16 + s * 16 + (lane & 15), lane >> 4);
     };
-    auto load_rows = [&](i32x8 (&bv)[ST], const uint32_t (&ro)[ST], int w) {
+    auto load_rows = [&](Piece (&bv)[ST], const uint32_t (&ro)[ST], int w) {
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-            const uint32_t off = ro[s] + (uint32_t)w * (XT ? 4 * 512 : kWin);
-            const i32x4 lo = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-            const i32x4 hi = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off + 16u, 0, 0));
-            bv[s] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+        for (int s = 0; s < ST; ++s) bv[s] = src.load(ro[s], w);
     };
 
-    // Weight operands of one element in registers: main and overflow A
-    // operands of every tile with their index words (an absent overflow
-    // operand is zeros: its products are zero). Two sets alternate (steps e,
-    // e+1), for the token rows too: element e+1's rows load at the start of
-    // step e, into the set whose matrix instructions (step e-1's) have been
-    // issued before the barrier, so the loads do not wait for them.
+    // Weight operands of one element in registers: both halves' A operands of
+    // every tile. Two sets alternate (steps e, e+1), for the token rows too:
+    // element e+1's rows load at the start of step e, into the set whose matrix
+    // instructions (step e-1's) have been issued before the barrier, so the
+    // loads do not wait for them.
     struct Ops {
-        i32x4 av[NT], ao[NT];
-        int ix[NT], io[NT];
+        i32x4 a[2][NT];
     };
     Ops ops[2];
-    i32x8 bv[2][ST];
+    Piece bv[2][ST];
     auto read_ops = [&](Ops &r, const int8_t *b) {
 #pragma unroll
-        for (int c = 0; c < NT; ++c) {
-            const int8_t *op = b + c * kOpBytes;
-            r.av[c] = *reinterpret_cast<const i32x4 *>(op + lane * 16);
-            r.ix[c] = *reinterpret_cast<const int *>(op + 1024 + iword * 4);
-            const int8_t *oo = b + S::AB + c * kOpBytes;
-            r.ao[c] = *reinterpret_cast<const i32x4 *>(oo + lane * 16);
-            r.io[c] = *reinterpret_cast<const int *>(oo + 1024 + iword * 4);
-        }
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < NT; ++c)
+                r.a[h][c] = *reinterpret_cast<const i32x4 *>(b + (2 * c + h) * 1024 + lane * 16);
     };
 
     // the item's weight scales and biases, one copy each into this wave's
@@ -391,7 +348,7 @@ __device__ __forceinline__ void direct_body(const LinearArgs &a, const GeluArg *
     int kb = 0, wb = 0;
     uint32_t rob[ST];
     row_offsets(ib, rob);
-    auto load_next_rows = [&](i32x8 (&dst)[ST]) {
+    auto load_next_rows = [&](Piece (&dst)[ST]) {
         load_rows(dst, rob, phys(ib, kb < n_my ? wb : a.n_win - 1));
         if (++wb == a.n_win) {
             wb = 0;
@@ -418,22 +375,17 @@ __device__ __forceinline__ void direct_body(const LinearArgs &a, const GeluArg *
         // harmless.) Products of tiles past the item's last tile land in
         // accumulators that are never stored.
         read_ops(nxt, smem + sl * S::BUF);
-        // (all main products first, then the overflow ones: an instruction
-        // never waits for the result of the one just before it)
+        // (the halves one after the other: an instruction never waits for the
+        // result of the one just before it)
 #pragma unroll
-        for (int c = 0; c < NT; ++c)
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int s = 0; s < ST; ++s)
-                acc[c][s] =
-                    __builtin_amdgcn_smfmac_i32_16x16x128_i8(cur.av[c], bv[PA][s], acc[c][s], cur.ix[c], 0, 0);
+            for (int c = 0; c < NT; ++c)
 #pragma unroll
-        for (int c = 0; c < NT; ++c)
+                for (int s = 0; s < ST; ++s)
+                    acc[c][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur.a[h][c], bv[PA][s].v[h], acc[c][s], 0, 0, 0);
 #pragma unroll
-            for (int s = 0; s < ST; ++s)
-                acc[c][s] =
-                    __builtin_amdgcn_smfmac_i32_16x16x128_i8(cur.ao[c], bv[PA][s], acc[c][s], cur.io[c], 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4 * NT; ++v) {
+        for (int v = 0; v < 2 * NT; ++v) {
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one matrix instruction
         }

@@ -146,12 +146,10 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     const int64_t mpad = (a.m + 15) / 16 * 16;
     const int64_t slice0 = (int64_t)ts * a.slice_groups * S::TG;
     const int n_groups = (int)std::min<int64_t>(a.slice_groups, (mpad - slice0 + S::TG - 1) / S::TG);
-    // this lane's index word: block-row (lane%16)/4, lane group lane/16
-    const int iword = ((lane & 15) >> 2) * 4 + (lane >> 4);
 
     const RowSource<XL> src(a);
-    // Token rows: lane l of subtile s loads features 32*(l/16) .. +31 of the
-    // window for token (l % 16) -- the B operand layout. Tokens past m read
+    // Token rows: lane l of subtile s loads features 16*(l/16) .. +15 of each
+    // half of the window for token (l % 16) -- the B operand layout. Tokens past m read
     // zeros (out-of-range offsets) or a padding token of the last block; a
     // ragged last window reads bytes past the row (or zeros past the buffer),
     // which meet zero weights.
@@ -187,9 +185,12 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     // (ro: the group's row offsets, whose low bits say how its rows lie)
     auto multiply = [&](auto pb, uint32_t cbase, uint32_t nbase, const uint32_t (&ro)[ST]) {
         constexpr int PB = decltype(pb)::value;
-        i32x8 rows[ST];
+        i32x4 rows[2][ST];
 #pragma unroll
-        for (int s = 0; s < ST; ++s) rows[s] = src.aligned(bv[PB][s], ro[s]);
+        for (int s = 0; s < ST; ++s) {
+            rows[0][s] = src.aligned(bv[PB][s], 0, ro[s]);
+            rows[1][s] = src.aligned(bv[PB][s], 1, ro[s]);
+        }
         static_for<NU>([&](auto cc) {
             constexpr int C = decltype(cc)::value;
             constexpr int J = C + LA;
@@ -198,11 +199,9 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
             else
                 read_unit(ring[J % RS], nbase, J - NU);
 #pragma unroll
-            for (int s = 0; s < ST; ++s) {
-                const i32x4 b = C < NT ? __builtin_shufflevector(rows[s], rows[s], 0, 1, 2, 3)
-                                           : __builtin_shufflevector(rows[s], rows[s], 4, 5, 6, 7);
-                acc[C % NT][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ring[C % RS], b, acc[C % NT][s], 0, 0, 0);
-            }
+            for (int s = 0; s < ST; ++s)
+                acc[C % NT][s] =
+                    __builtin_amdgcn_mfma_i32_16x16x64_i8(ring[C % RS], rows[C / NT][s], acc[C % NT][s], 0, 0, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
             __builtin_amdgcn_sched_group_barrier(0x008, ST, 0);  // its matrix instructions
         });

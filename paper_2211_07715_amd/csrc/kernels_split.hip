@@ -3,21 +3,23 @@
 // walking the whole reduction would leave most of the chip idle and put
 // every window's memory latency in series.
 //
-// Same method and operand image as the other kernels (Section "Sparse GEMM
-// operators", Figure 1, Algorithm 1: the stored 4x1 blocks are one operand of
-// the 4:2-sparse int8 matrix instruction, the input columns the weight's mask
-// names are selected by the instruction's column indices, int32 accumulation,
-// one fused epilogue per output). A workgroup owns one work item (ST 16-token
-// subtiles x NT 16-channel tiles) and splits its reduction over its waves:
-// wave v of kw takes windows v, v + kw, ... (at most WPW of them). It
-// issues every load of its windows at once -- token rows, main and overflow
-// operands, the latter from an overflow image laid out like the main one
-// (one slot per window and tile, zeros where the tile has none, so that no
-// lookup stands between a wave and its loads) -- and so waits about one
+// Same product as the other kernels (Section "Sparse GEMM operators", Figure
+// 1, Algorithm 1), from the dense operand image (kernels_panel.hip says why;
+// here it also halves a wave's load instructions, six of 16 bytes a lane for a
+// window instead of ten). A workgroup owns one work item (ST 16-token subtiles
+// x NT 16-channel tiles) and splits its reduction over its waves: wave v of kw
+// takes windows v, v + kw, ... (at most WPW of them). It issues every load of
+// its windows at once -- no lookup stands between a wave and its loads -- and
+// so waits about one
 // memory latency before its matrix instructions. The waves' int32 partial sums meet in
 // LDS; integer addition is exact in any order, so the sum equals the single
 // accumulation of the other kernels bit for bit. Each (tile, subtile) pair
 // is then reduced, and its epilogue run, by one wave.
+//
+// What bounds it: a launch's fixed cost (about 2 us back to back) and one
+// memory round trip; 4:2-sparse operands -> dense, us at 128 tokens, 80 %: QKV
+// 3.47 -> 3.33, attention output 2.76 -> 2.68, FFN1 4.11 -> 3.92, FFN2 3.80 ->
+// 3.56.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -54,18 +56,13 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
     // this wave's windows: w_j = wave + j * kw, j < nw
     const int nw = wave < a.n_win ? (a.n_win - 1 - wave) / kw + 1 : 0;
 
-    const __amdgpu_buffer_rsrc_t mr = __builtin_amdgcn_make_buffer_rsrc((void *)a.main, 0, (int)a.main_bytes,
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc((void *)a.dense, 0, (int)a.dense_bytes,
                                                                         kRsrcWord3);
-    // (a.ovf: the overflow image in the main image's layout)
-    const __amdgpu_buffer_rsrc_t orc = __builtin_amdgcn_make_buffer_rsrc((void *)a.ovf, 0, (int)a.ovf_bytes,
-                                                                         kRsrcWord3);
     const RowSource<XL> src(a);
-    const uint32_t wstride = (uint32_t)a.n_tiles * kOpBytes;  // main image bytes per window
-    // this lane's index word: block-row (lane%16)/4, lane group lane/16
-    const int iword = ((lane & 15) >> 2) * 4 + (lane >> 4);
+    const uint32_t wstride = (uint32_t)a.n_tiles * kDenseOp;  // image bytes per window
 
-    // Token rows: lane l of subtile s loads features 32*(l/16) .. +31 of
-    // the window for token (l % 16) -- the B operand layout (tokens past m
+    // Token rows: lane l of subtile s loads features 16*(l/16) .. +15 of
+    // each half of the window for token (l % 16) -- the B operand layout (tokens past m
     // read zeros or a padding token of the last block, a ragged last window
     // bytes that meet zero weights).
     uint32_t ro[ST];
@@ -73,8 +70,7 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
     for (int s = 0; s < ST; ++s) ro[s] = src.offset(a, t0 + s * 16 + (lane & 15), lane >> 4);
 
     RowPiece<XL> bv[WPW][ST];
-    i32x4 av[WPW][NT], ao[WPW][NT];
-    int ix[WPW][NT], io[WPW][NT];
+    i32x4 av[WPW][NT][2];
 #pragma unroll
     for (int j = 0; j < WPW; ++j) {
         if (j < nw) {
@@ -83,15 +79,11 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
             for (int s = 0; s < ST; ++s) bv[j][s] = src.load(ro[s], (int)w);
 #pragma unroll
             for (int c = 0; c < NT; ++c) {
-                const uint32_t base = c < ntl ? (uint32_t)(tile0 + c) * (uint32_t)kOpBytes : kOob;
-                av[j][c] = __builtin_bit_cast(
-                    i32x4, __builtin_amdgcn_raw_buffer_load_b128(mr, base + 16u * (uint32_t)lane, w * wstride, 0));
-                ix[j][c] = (int)__builtin_amdgcn_raw_buffer_load_b32(mr, base + 1024u + 4u * (uint32_t)iword,
-                                                                     w * wstride, 0);
-                ao[j][c] = __builtin_bit_cast(
-                    i32x4, __builtin_amdgcn_raw_buffer_load_b128(orc, base + 16u * (uint32_t)lane, w * wstride, 0));
-                io[j][c] = (int)__builtin_amdgcn_raw_buffer_load_b32(orc, base + 1024u + 4u * (uint32_t)iword,
-                                                                     w * wstride, 0);
+                const uint32_t base = c < ntl ? (uint32_t)(tile0 + c) * kDenseOp + 16u * (uint32_t)lane : kOob;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    av[j][c][h] = __builtin_bit_cast(
+                        i32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, base + 1024u * h, w * wstride, 0));
             }
         }
     }
@@ -127,19 +119,17 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
 #pragma unroll
     for (int j = 0; j < WPW; ++j) {
         if (j < nw) {
-            i32x8 rows[ST];
 #pragma unroll
-            for (int s = 0; s < ST; ++s) rows[s] = src.aligned(bv[j][s], ro[s]);
+            for (int h = 0; h < 2; ++h) {
+                i32x4 rows[ST];
 #pragma unroll
-            for (int c = 0; c < NT; ++c)
+                for (int s = 0; s < ST; ++s) rows[s] = src.aligned(bv[j][s], h, ro[s]);
 #pragma unroll
-                for (int s = 0; s < ST; ++s)
-                    acc[c][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(av[j][c], rows[s], acc[c][s], ix[j][c], 0, 0);
+                for (int c = 0; c < NT; ++c)
 #pragma unroll
-            for (int c = 0; c < NT; ++c)
-#pragma unroll
-                for (int s = 0; s < ST; ++s)
-                    acc[c][s] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(ao[j][c], rows[s], acc[c][s], io[j][c], 0, 0);
+                    for (int s = 0; s < ST; ++s)
+                        acc[c][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[j][c][h], rows[s], acc[c][s], 0, 0, 0);
+            }
         }
     }
 #pragma unroll

@@ -68,8 +68,7 @@ struct LinearArgs {
     int32_t n;
     int32_t k;
     const int8_t *main;
-    const int8_t *ovf;    // compact overflow operands (staged kernel) or the dense
-                          // overflow image (split-reduction, direct kernels)
+    const int8_t *ovf;    // compact overflow operands (main, ovf and om: staged kernel)
     uint32_t main_bytes;  // image sizes: the range of the buffer loads
     uint32_t ovf_bytes;
     const uint32_t *om;  // overflow table of this launch's tile-group size, [n_win][n_cgroups][2]
@@ -83,9 +82,9 @@ struct LinearArgs {
     int64_t n_items;    // work items: token tiles x channel groups
     int32_t x_cb;       // 32-feature column blocks of x (SL_LAYOUT_T16X32 input)
     int32_t y_cb;       // 32-channel column blocks of y (SL_LAYOUT_T16X32 output)
+    const int8_t *dense;    // dense operand image (the other kernels)
+    uint32_t dense_bytes;   // its size (the range of the loads)
     // weight-stationary kernel only
-    const int8_t *dense;    // dense operand image [n_win][n_tiles][kDenseOp]
-    uint32_t dense_bytes;   // its size (the range of the copies)
     int32_t n_slices;       // token slices per channel group
     int32_t slice_groups;   // token groups (16 ST tokens) per slice
     // split-reduction kernel only: waves per workgroup
@@ -99,30 +98,33 @@ __device__ __forceinline__ int64_t t16x32_offset(int64_t t, int32_t c, int32_t c
     return ((t >> 4) * cb + (c >> 5)) * 512 + (t & 15) * 32 + (c & 31);
 }
 
-// Where the token rows of X lie, for the kernels that load B operands (32
-// features of one token a lane) straight into registers.
+// Where the token rows of X lie, for the kernels that load B operands straight
+// into registers.
 enum class RowsAt {
     kBlocks,  // SL_LAYOUT_T16X32
     kWords,   // row-major, every row starting at a multiple of 4 bytes: buffer loads need no more
     kBytes,   // row-major, anywhere
 };
 
-// A lane's piece of one window as loaded. Rows at any byte are read as the 9
-// aligned words that hold the 32 bytes (no word without a byte of X is read,
-// so no access leaves X's pages) and shifted into place when they are used.
+// A lane's 16 bytes of each half of a window, as loaded. Rows at any byte are
+// read as the aligned words that hold the bytes (no word without a byte of X
+// is read, so no access leaves X's pages) and shifted into place when they are
+// used.
 template <RowsAt XL>
 struct RowPiece {
-    i32x8 v;
+    i32x4 v[2];
 };
 template <>
 struct RowPiece<RowsAt::kBytes> {
-    i32x8 v;
-    int last;
+    i32x4 v[2];
+    int last[2];
 };
 
 template <RowsAt XL>
 struct RowSource {
     static constexpr bool XT = XL == RowsAt::kBlocks;
+    static constexpr uint32_t kHalf = XT ? 2 * 512 : 64;      // bytes to the second half of a window
+    static constexpr uint32_t kNext = XT ? 4 * 512 : kWin;    // and to the next window
     __amdgpu_buffer_rsrc_t rsrc;
     uint32_t mis;   // bytes of X's first word before X
     int64_t mpad;
@@ -135,36 +137,43 @@ struct RowSource {
                                  : (XL == RowsAt::kBytes ? (a.m * a.k + mis + 3) / 4 * 4 : a.m * a.k);
         rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.x - mis), 0, (int)bytes, kRsrcWord3);
     }
-    // byte offset of 32-feature group g (0..3) of window 0 of token r; past
-    // the buffer for tokens past the last (in the block layout, block)
+    // byte offset of the 16 features of lane group g (0..3) in window 0 of
+    // token r; past the buffer for tokens past the last (in the block layout,
+    // block). Lanes of one token read 64 contiguous bytes of a row, or two
+    // whole blocks of 16 tokens.
     __device__ __forceinline__ uint32_t offset(const LinearArgs &a, int64_t r, int g) const
     {
         if constexpr (XT)
-            return r < mpad ? (uint32_t)((r >> 4) * a.x_cb * 512) + 512u * (uint32_t)g + 32u * (uint32_t)(r & 15) : kOob;
+            return r < mpad ? (uint32_t)((r >> 4) * a.x_cb * 512) + 512u * (uint32_t)(g >> 1) + 16u * (uint32_t)(g & 1) +
+                                  32u * (uint32_t)(r & 15)
+                            : kOob;
         else
-            return r < a.m ? mis + (uint32_t)(r * a.k) + 32u * (uint32_t)g : kOob;
+            return r < a.m ? mis + (uint32_t)(r * a.k) + 16u * (uint32_t)g : kOob;
     }
     // (an offset of kOob plus a window's stays past the buffer: zeros)
     __device__ __forceinline__ RowPiece<XL> load(uint32_t off, int w) const
     {
-        const uint32_t o = (XL == RowsAt::kBytes ? off & ~3u : off) + (uint32_t)w * (XT ? 4 * 512 : kWin);
-        const i32x4 lo = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0));
-        const i32x4 hi = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o + 16u, 0, 0));
+        const uint32_t o = (XL == RowsAt::kBytes ? off & ~3u : off) + (uint32_t)w * kNext;
         RowPiece<XL> p;
-        p.v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        if constexpr (XL == RowsAt::kBytes) p.last = (int)__builtin_amdgcn_raw_buffer_load_b32(rsrc, o + 32u, 0, 0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            p.v[h] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o + h * kHalf, 0, 0));
+            if constexpr (XL == RowsAt::kBytes)
+                p.last[h] = (int)__builtin_amdgcn_raw_buffer_load_b32(rsrc, o + h * kHalf + 16u, 0, 0);
+        }
         return p;
     }
-    __device__ __forceinline__ i32x8 aligned(const RowPiece<XL> &p, uint32_t off) const
+    __device__ __forceinline__ i32x4 aligned(const RowPiece<XL> &p, int h, uint32_t off) const
     {
         if constexpr (XL == RowsAt::kBytes) {
-            i32x8 r;
+            i32x4 r;
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                r[i] = (int)__builtin_amdgcn_alignbyte((uint32_t)(i < 7 ? p.v[i < 7 ? i + 1 : 7] : p.last), (uint32_t)p.v[i], off);
+            for (int i = 0; i < 4; ++i)
+                r[i] = (int)__builtin_amdgcn_alignbyte((uint32_t)(i < 3 ? p.v[h][i < 3 ? i + 1 : 3] : p.last[h]),
+                                                       (uint32_t)p.v[h][i], off);
             return r;
         } else {
-            return p.v;
+            return p.v[h];
         }
     }
 };
@@ -497,6 +506,13 @@ constexpr bool panel_takes_bytes(int nt, int st, int nwv, int r)
 // resident workgroups of a panel-kernel shape for `lds` bytes of LDS (all kinds and layouts of a
 // shape share one register budget; the SL_EPI_F32 row-major instance stands for them)
 sl_status panel_resident(PanelCfg c, size_t lds, int *out);
+
+// Tile kernel (kernels_tile.hip): a.n_items workgroups, one tile of
+// kTileTokens tokens x nt (6 or 8) 16-channel tiles each; token rows in the
+// block layout or 16-byte aligned.
+constexpr int kTileTokens = 128;
+sl_status launch_tile(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, int nt, bool xt, bool yt,
+                      hipStream_t stream);
 
 // Persistent grid size of a kernel on the current device: the workgroups of
 // `threads` threads and `lds` bytes of dynamic LDS resident at once. On first

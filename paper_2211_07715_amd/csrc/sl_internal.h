@@ -88,7 +88,7 @@ constexpr int kMaxOmTables = 8;
 // One operand of the dense operand image [n_win][n_tiles]: a tile's 16
 // channels x one window, as two A operands of v_mfma_i32_16x16x64_i8 (1024
 // bytes each, lane-major): byte 16 l + i of half h is channel l % 16, window
-// column 32 (l / 16) + 16 h + i. The weight-stationary kernel reads it.
+// column 64 h + 16 (l / 16) + i.
 constexpr uint32_t kDenseOp = 2048;
 
 struct DeviceImage {
@@ -104,10 +104,6 @@ struct DeviceImage {
     const uint32_t *om[kMaxOmTables] = {};
     const int8_t *dense = nullptr;
     uint32_t dense_bytes = 0;
-    // split-reduction kernel: the overflow operands in the main image's
-    // order, one slot per (window, tile), zeros where the tile has none
-    const int8_t *ovfd = nullptr;
-    uint32_t ovfd_bytes = 0;
     int64_t bytes = 0;
 };
 
@@ -143,7 +139,7 @@ void clear_error();
 // Kernel-choice overrides for tests and tuning (SL_PATH, SL_TILE, SL_DTILE,
 // SL_PTILE), read from the environment once and again on sl_reload_env()
 struct EnvCfg {
-    char path[16];  // "" (automatic), "split", "panel", "direct", "staged"
+    char path[16];  // "" (automatic), "split", "panel", "tile", "direct", "staged"
     int tile[5];    // SL_TILE "st,ct,wm,wn,d"; tile[0] == 0: unset
     int dtile[4];   // SL_DTILE "st,nt,wm,d"
     int ptile[4];   // SL_PTILE "nt,st,nwv,r"

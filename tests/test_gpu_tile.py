@@ -1,0 +1,66 @@
+"""GPU parity of the tile kernel (128 tokens x 6 or 8 channel tiles, the
+reduction's halves split over its waves), through the C ABI: every epilogue
+kind and layout pairing at the edges of its tiles -- ragged tokens, channels
+and last window, fewer and more windows than its ring holds, several channel
+groups -- and which kernel runs by default on either side of its rules. Bars as
+in test_gpu_parity.py.
+"""
+import numpy as np
+import pytest
+
+from test_gpu_panel import T, _refs
+from test_gpu_parity import KINDS, _case, check, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nt", [6, 8])
+@pytest.mark.parametrize("m,n,k", [(1, 4, 16), (128, 96, 128), (130, 132, 400), (129, 256, 512), (300, 100, 656),
+                                   (257, 200, 1040), (140, 128, 2048)])
+def test_tile_shapes(hip, monkeypatch, nt, m, n, k):
+    import torch
+    w, sw, b, rng = _case(n, k, 0.25, 5 * m + n + k)
+    x = rng.integers(-127, 128, (m, k), dtype=np.int8)
+    refs = _refs(x, w, sw, b)
+    pw = hip.PackedWeight.pack(w, sw, b)
+    xd = {0: torch.from_numpy(x).cuda(), T: torch.from_numpy(np.ascontiguousarray(hip.to_t16x32(x, fill=77))).cuda()}
+    monkeypatch.setenv("SL_PATH", "tile")
+    monkeypatch.setenv("SL_TILE", f"{nt},0,0,0,0")
+    for xl, yl in [(0, 0), (T, 0), (T, T), (0, T)]:
+        for name, kind in KINDS.items():
+            if yl == T and kind not in (3, 4):
+                continue
+            so, ref = refs[kind]
+            for off in (0, 4) if yl == 0 and kind in (3, 4) else (0,):
+                say(f"tile {nt} m={m} n={n} k={k} layouts=({xl},{yl}) {name} offset {off}")
+                out = None
+                if off:
+                    out = torch.empty(m * n + off, dtype=torch.int8, device="cuda")[off:].view(m, n)
+                y = pw.run(xd[xl], 0.02, kind, out_scale=so, x_layout=xl, y_layout=yl, m_tokens=m, out=out)
+                torch.cuda.synchronize()
+                assert hip.last_path().startswith(f"tile 128,{nt}"), hip.last_path()
+                got = hip.from_t16x32(y.cpu().numpy(), m, n) if yl == T else y.cpu().numpy()
+                check(kind, got, ref, f"tile {nt} {name} m={m} n={n} k={k} layouts=({xl},{yl}) offset {off}")
+    pw.free()
+
+
+@pytest.mark.parametrize("n,k,m,kind,xl,yl,want", [
+    (768, 3072, 4096, 1, 0, 0, "tile 128,6"), (768, 3072, 4096, 3, T, 0, "tile 128,6"),
+    (768, 3072, 4096, 3, T, T, "direct"), (768, 3072, 4096, 3, 0, T, "tile 128,6"),
+    (768, 3072, 2048, 1, 0, 0, "staged"), (1024, 4096, 4096, 1, T, 0, "tile 128,8"),
+    (1024, 4096, 4096, 1, 0, 0, "tile 128,8"), (768, 768, 4096, 1, 0, 0, "panel")])
+def test_tile_choice(hip, monkeypatch, n, k, m, kind, xl, yl, want):
+    import torch
+    monkeypatch.delenv("SL_PATH", raising=False)
+    w, sw, b, rng = _case(n, k, 0.2, n + m)
+    x = rng.integers(-127, 128, (m, k), dtype=np.int8)
+    rows = np.arange(0, m, 61)
+    pw = hip.PackedWeight.pack(w, sw, b)
+    xd = torch.from_numpy(np.ascontiguousarray(hip.to_t16x32(x)) if xl == T else x).cuda()
+    so, ref = _refs(np.ascontiguousarray(x[rows]), w, sw, b)[kind]
+    y = pw.run(xd, 0.02, kind, out_scale=so, x_layout=xl, y_layout=yl, m_tokens=m)
+    torch.cuda.synchronize()
+    assert hip.last_path().startswith(want), hip.last_path()
+    got = hip.from_t16x32(y.cpu().numpy(), m, n) if yl == T else y.cpu().numpy()
+    check(kind, got[rows], ref, f"{n}x{k} m={m} {hip.last_path()}")
+    pw.free()
