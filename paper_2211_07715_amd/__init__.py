@@ -47,6 +47,7 @@ EXPORTS = ("sparse_linear_pack", "sparse_linear_pack_host", "sparse_linear_run",
 # kernel-selection overrides the library reads from the environment
 ENV_KEYS = ("SL_PATH", "SL_TILE", "SL_DTILE", "SL_PTILE", "SL_PSLICES")
 _env_seen: Optional[tuple] = None
+_env_getters: Optional[tuple] = None
 
 _lib: Optional[ctypes.CDLL] = None
 
@@ -103,8 +104,18 @@ def load() -> ctypes.CDLL:
 def _sync_env(lib: ctypes.CDLL):
     """The library reads SL_PATH / SL_*TILE once; have it read them again when
     this process has changed them since the last run."""
-    global _env_seen
-    now = tuple(os.environ.get(k) for k in ENV_KEYS)
+    global _env_seen, _env_getters
+    # (os.environ encodes and decodes on every read, 0.4 us a key: the mapping
+    # of encoded names that it keeps is read where there is one)
+    if _env_getters is None or _env_getters[0] is not os.environ:
+        data = getattr(os.environ, "_data", None)
+        keys = tuple(os.fsencode(k) for k in ENV_KEYS)
+        if type(data) is dict and all(isinstance(k, bytes) for k in data):
+            _env_getters = (os.environ, data.get, *keys)
+        else:
+            _env_getters = (os.environ, os.environ.get, *ENV_KEYS)
+    _, get, k0, k1, k2, k3, k4 = _env_getters
+    now = (get(k0), get(k1), get(k2), get(k3), get(k4))
     if now != _env_seen:
         lib.sl_reload_env()
         _env_seen = now
@@ -140,11 +151,34 @@ def from_t16x32(b: np.ndarray, rows: int, cols: int) -> np.ndarray:
     return np.ascontiguousarray(b.transpose(0, 2, 1, 3).reshape(rb * 16, cb * 32)[:rows, :cols])
 
 
-def _stream_ptr(stream) -> Optional[int]:
+_torch = None      # set by _torch_once()
+_raw_stream = None  # () -> the current device's current stream, as an integer
+_KIND_DTYPE: dict = {}
+
+
+def _torch_once():
+    """Import torch at the first call that needs it, and look up once what every call asks it for."""
+    global _torch, _raw_stream
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    _KIND_DTYPE.update({EPI_ACC_I32: torch.int32, EPI_F32: torch.float32, EPI_F32_GELU: torch.float32,
+                        EPI_I8: torch.int8, EPI_I8_GELU: torch.int8})
+    # torch.cuda.current_stream() makes a Stream object to hold the number that
+    # torch's own launches read directly (3.2 against 0.2 us a call)
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None:
+        _raw_stream = lambda: raw(device())
+    else:
+        _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+    _torch = torch
+    return torch
+
+
+def _stream_ptr(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        _torch_once()
+    return _raw_stream()
 
 
 class PackedWeight:
@@ -226,7 +260,7 @@ class PackedWeight:
         x: [M, k_in] (LAYOUT_ROWS) or t16x32_shape(M, k_in) with m_tokens=M
         (LAYOUT_T16X32). Y: [M, n_out] of the kind's dtype, or, for the int8
         kinds with y_layout=LAYOUT_T16X32, t16x32_shape(M, n_out) int8."""
-        import torch
+        torch = _torch or _torch_once()
         if x.dtype != torch.int8 or not x.is_cuda or not x.is_contiguous():
             raise ValueError("x must be a contiguous CUDA int8 tensor")
         if x_layout == LAYOUT_ROWS:
@@ -243,8 +277,7 @@ class PackedWeight:
                 raise ValueError(f"x must have shape {t16x32_shape(m, self.k_in)}")
         else:
             raise ValueError(f"unknown x_layout {x_layout}")
-        dt = {EPI_ACC_I32: torch.int32, EPI_F32: torch.float32, EPI_F32_GELU: torch.float32,
-              EPI_I8: torch.int8, EPI_I8_GELU: torch.int8}[kind]
+        dt = _KIND_DTYPE[kind]
         shape = t16x32_shape(m, self.n_out) if y_layout == LAYOUT_T16X32 else (m, self.n_out)
         if out is None:
             out = torch.empty(shape, dtype=dt, device=x.device)
@@ -252,10 +285,10 @@ class PackedWeight:
             raise ValueError("out has the wrong dtype/shape or is not contiguous")
         lib = load()
         _sync_env(lib)
-        _check(lib.sparse_linear_run_layout(self.handle, ctypes.c_void_p(x.data_ptr()), int(x_layout), m,
-                                               float(x_scale), int(kind), float(out_scale),
-                                               ctypes.c_void_p(out.data_ptr()), int(y_layout), _stream_ptr(stream)),
-               "sparse_linear_run_layout")
+        st = lib.sparse_linear_run_layout(self.handle, x.data_ptr(), int(x_layout), m, float(x_scale), int(kind),
+                                          float(out_scale), out.data_ptr(), int(y_layout), _stream_ptr(stream))
+        if st != SL_OK:
+            _check(st, "sparse_linear_run_layout")
         return out
 
 
@@ -281,7 +314,7 @@ def quantize_act(x, scale: float, out=None, stream=None, layout: int = LAYOUT_RO
     """q = clamp(rint(x / scale), -127, 127) for a contiguous CUDA fp32 tensor:
     same shape (LAYOUT_ROWS), or, for a 2-D x [rows, cols] and
     layout=LAYOUT_T16X32, int8 of shape t16x32_shape(rows, cols)."""
-    import torch
+    torch = _torch or _torch_once()
     if x.dtype != torch.float32 or not x.is_cuda or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA float32 tensor")
     if layout == LAYOUT_ROWS:
@@ -289,8 +322,8 @@ def quantize_act(x, scale: float, out=None, stream=None, layout: int = LAYOUT_RO
             out = torch.empty(x.shape, dtype=torch.int8, device=x.device)
         elif out.dtype != torch.int8 or out.numel() != x.numel() or not out.is_contiguous():
             raise ValueError("out must be a contiguous int8 tensor with x's size")
-        _check(load().quantize_act(ctypes.c_void_p(x.data_ptr()), x.numel(), float(scale),
-                                   ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)), "quantize_act")
+        _check(load().quantize_act(x.data_ptr(), x.numel(), float(scale), out.data_ptr(), _stream_ptr(stream)),
+               "quantize_act")
         return out
     if layout != LAYOUT_T16X32 or x.dim() != 2:
         raise ValueError("LAYOUT_T16X32 quantisation takes a 2-D x [rows, cols]")
@@ -300,7 +333,7 @@ def quantize_act(x, scale: float, out=None, stream=None, layout: int = LAYOUT_RO
         out = torch.empty(shape, dtype=torch.int8, device=x.device)
     elif out.dtype != torch.int8 or tuple(out.shape) != shape or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous int8 tensor of shape {shape}")
-    _check(load().quantize_act_layout(ctypes.c_void_p(x.data_ptr()), rows, cols, float(scale),
-                                      ctypes.c_void_p(out.data_ptr()), int(layout), _stream_ptr(stream)),
+    _check(load().quantize_act_layout(x.data_ptr(), rows, cols, float(scale), out.data_ptr(), int(layout),
+                                      _stream_ptr(stream)),
            "quantize_act_layout")
     return out
