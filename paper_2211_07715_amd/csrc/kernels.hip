@@ -1037,7 +1037,8 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
             const int64_t nwg = n_cg * t.n_slices;
             if (nwg > 0x7fffffff) continue;
             // busy CUs and the bytes each reads
-            const double cus = (double)std::min<int64_t>(n_cu, nwg);
+            double cus = (double)std::min<int64_t>(n_cu, nwg);
+            if (xl != RowsAt::kBlocks) cus = (double)nwg / (double)((nwg + n_cu - 1) / n_cu);
             const double bytes = (xl == RowsAt::kBlocks ? 1.0 : 3.0) * (double)a.m * w->k_in * n_cg + (double)nwg * (double)panel;
             // waves per workgroup without a token group idle; among shapes
             // that read the same bytes, more resident waves a SIMD hide more
