@@ -1007,7 +1007,7 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
         const bool bytes_at = xl == RowsAt::kBytes;
         if (bytes_at ? !panel_takes_bytes(c.nt, c.st, c.nwv, c.r) : !have_forced && c.nt == 8) continue;  // (8: below)
         const uint64_t panel = (uint64_t)ti.n_win * c.nt * kDenseOp;
-        const size_t lds = panel_lds_bytes(c, run_kind, yt, panel);
+        const size_t lds = panel_lds_bytes(c, run_kind, xl, yt, panel);
         if (lds > kLdsMax) continue;
         // resident workgroups per device, cached per (device, shape, LDS size)
         static thread_local struct {
@@ -1064,7 +1064,7 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
         const bool lines = i8 && !yt;
         const PanelCfg c8 = lines ? PanelCfg{8, 2, 8, 2} : PanelCfg{8, 2, 12, 2};
         const int64_t n_cg = (ti.n_tiles + 7) / 8;
-        const size_t lds = panel_lds_bytes(c8, run_kind, yt, (uint64_t)ti.n_win * 8 * kDenseOp);
+        const size_t lds = panel_lds_bytes(c8, run_kind, xl, yt, (uint64_t)ti.n_win * 8 * kDenseOp);
         LinearArgs t = a;
         set_panel_slices(t, c8, n_cg, std::max<int64_t>(1, n_cu / n_cg));
         // tile products of the busiest SIMD (a workgroup's groups go round its SIMDs)

@@ -187,7 +187,7 @@ __device__ __forceinline__ void direct_body(const LinearArgs &a, const GeluArg *
     // past m read zeros (out-of-range offsets) or a padding token of the last
     // block; a ragged last window reads bytes past the row (or zeros past the
     // buffer), which meet zero weights.
-    using Rows = RowSource<XT ? RowsAt::kBlocks : RowsAt::kWords>;
+    using Rows = RowSource<XT ? RowsAt::kBlocks : RowsAt::kWords, false>;
     using Piece = RowPiece<XT ? RowsAt::kBlocks : RowsAt::kWords>;
     const Rows src(a);
     auto row_offsets = [&](const ItemIter &it, uint32_t (&ro)[ST]) {

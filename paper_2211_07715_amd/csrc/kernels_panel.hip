@@ -65,14 +65,22 @@ constexpr bool panel_transposes()
     return NT % 2 == 0 && EpiOut<KIND>::kBytes == 4 && KIND != SL_EPI_F32_GELU && !YT;
 }
 
-// LDS layout: weight scales and biases | GELU step table | per-wave transpose
-// areas | panel
-template <int KIND, int NT, int ST, int NWV, bool YT>
+// Row-major token rows change lanes through LDS for 4-byte outputs (us, without
+// -> with: int32 QKV at 2048 tokens 10.2 -> 9.3, fp32 GELU FFN1 at 3072 20.1 ->
+// 18.5); with int8 outputs, whose waves spend less on stores and more on
+// arithmetic, the extra LDS steps cost as much as they save or more (FFN1 at
+// 4096 17.9 -> 18.3, BERT-large FFN1 at 49152 222 -> 240).
+template <int KIND, RowsAt XL>
+using PanelRows = RowSource<XL, XL == RowsAt::kWords && EpiOut<KIND>::kBytes == 4>;
+
+// LDS layout: weight scales and biases | GELU step table | per-wave areas (the
+// transpose, and token rows that change lanes) | panel
+template <int KIND, int NT, int ST, int NWV, RowsAt XL, bool YT>
 struct PLds {
     using S = PShape<NT, ST, NWV>;
     static constexpr int kTab = KIND == SL_EPI_I8_GELU ? kGeluLds : 0;
-    static constexpr int kTr = panel_transposes<KIND, YT, NT>() ? NWV * S::TR : 0;
-    static constexpr int kFixed = S::VEC + kTab + kTr;
+    static constexpr int kWave = std::max(panel_transposes<KIND, YT, NT>() ? S::TR : 0, PanelRows<KIND, XL>::kScratch);
+    static constexpr int kFixed = S::VEC + kTab + NWV * kWave;
     static_assert(kFixed % 16 == 0, "the copies write 16-byte pieces");
     static size_t bytes(uint64_t panel) { return (size_t)kFixed + panel; }
 };
@@ -97,7 +105,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
 {
     constexpr bool XT = XL == RowsAt::kBlocks, UA = XL == RowsAt::kBytes;
     using S = PShape<NT, ST, NWV>;
-    using L = PLds<KIND, NT, ST, NWV, YT>;
+    using L = PLds<KIND, NT, ST, NWV, XL, YT>;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
 
     const int tid = threadIdx.x;
@@ -113,7 +121,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
 
     float *const vec = reinterpret_cast<float *>(smem);
     GeluCell *const tab = reinterpret_cast<GeluCell *>(smem + S::VEC);
-    int8_t *const trans = smem + S::VEC + L::kTab + wave * S::TR;
+    int8_t *const trans = smem + S::VEC + L::kTab + wave * L::kWave;
     int8_t *const panel = smem + L::kFixed;
 
     // ---- the group's panel: [window][tile] pairs of operands, copied global
@@ -147,7 +155,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     const int64_t slice0 = (int64_t)ts * a.slice_groups * S::TG;
     const int n_groups = (int)std::min<int64_t>(a.slice_groups, (mpad - slice0 + S::TG - 1) / S::TG);
 
-    const RowSource<XL> src(a);
+    const PanelRows<KIND, XL> src(a);
     // Token rows: lane l of subtile s loads features 16*(l/16) .. +15 of each
     // half of the window for token (l % 16) -- the B operand layout. Tokens past m read
     // zeros (out-of-range offsets) or a padding token of the last block; a
@@ -155,7 +163,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     // which meet zero weights.
     auto row_offsets = [&](int64_t t0, uint32_t (&ro)[ST]) {
 #pragma unroll
-        for (int s = 0; s < ST; ++s) ro[s] = src.offset(a, t0 + s * 16 + (lane & 15), lane >> 4);
+        for (int s = 0; s < ST; ++s) ro[s] = src.offset(a, t0 + s * 16 + src.load_token(lane), src.load_group(lane));
     };
     auto load_rows = [&](RowPiece<XL> (&bv)[ST], const uint32_t (&ro)[ST], int w) {
 #pragma unroll
@@ -188,8 +196,8 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
         i32x4 rows[2][ST];
 #pragma unroll
         for (int s = 0; s < ST; ++s) {
-            rows[0][s] = src.aligned(bv[PB][s], 0, ro[s]);
-            rows[1][s] = src.aligned(bv[PB][s], 1, ro[s]);
+            rows[0][s] = src.operand(bv[PB][s], 0, ro[s], trans, lane);
+            rows[1][s] = src.operand(bv[PB][s], 1, ro[s], trans, lane);
         }
         static_for<NU>([&](auto cc) {
             constexpr int C = decltype(cc)::value;
@@ -526,27 +534,36 @@ static sl_status launch_panel_kind(const LinearArgs &a, const GeluArg *ep, Panel
     return SL_ERR_UNSUPPORTED;
 }
 
-template <int KIND>
-static size_t panel_lds_kind(PanelCfg c, bool yt, uint64_t panel)
+template <int KIND, RowsAt XL, bool YT>
+static size_t panel_lds_shape(PanelCfg c, uint64_t panel)
 {
-#define SL_PANEL_LDS(NT_, ST_, NWV_, R_)                                                          \
-    if (c.nt == NT_ && c.st == ST_ && c.nwv == NWV_ && c.r == R_)                                 \
-        return yt ? PLds<KIND, NT_, ST_, NWV_, true>::bytes(panel)                               \
-                  : PLds<KIND, NT_, ST_, NWV_, false>::bytes(panel);
+#define SL_PANEL_LDS(NT_, ST_, NWV_, R_)                          \
+    if (c.nt == NT_ && c.st == ST_ && c.nwv == NWV_ && c.r == R_) \
+        return PLds<KIND, NT_, ST_, NWV_, XL, YT>::bytes(panel);
     SL_PANEL_SHAPES(SL_PANEL_LDS)
 #undef SL_PANEL_LDS
     return (size_t)-1;
 }
 
-size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, bool yt, uint64_t panel)
+template <int KIND, bool YT>
+static size_t panel_lds_kind(PanelCfg c, RowsAt xl, uint64_t panel)
+{
+    // (blocks and rows at any byte take the same)
+    return xl == RowsAt::kWords ? panel_lds_shape<KIND, RowsAt::kWords, YT>(c, panel)
+                                : panel_lds_shape<KIND, RowsAt::kBlocks, YT>(c, panel);
+}
+
+size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, RowsAt xl, bool yt, uint64_t panel)
 {
     switch (run_kind) {
-    case SL_EPI_ACC_I32: return panel_lds_kind<SL_EPI_ACC_I32>(c, false, panel);
-    case SL_EPI_F32: return panel_lds_kind<SL_EPI_F32>(c, false, panel);
-    case SL_EPI_F32_GELU: return panel_lds_kind<SL_EPI_F32_GELU>(c, false, panel);
-    case SL_EPI_I8: return panel_lds_kind<SL_EPI_I8>(c, yt, panel);
-    case SL_EPI_I8_GELU: return panel_lds_kind<SL_EPI_I8_GELU>(c, yt, panel);
-    default: return panel_lds_kind<kEpiI8GeluErf>(c, yt, panel);
+    case SL_EPI_ACC_I32: return panel_lds_kind<SL_EPI_ACC_I32, false>(c, xl, panel);
+    case SL_EPI_F32: return panel_lds_kind<SL_EPI_F32, false>(c, xl, panel);
+    case SL_EPI_F32_GELU: return panel_lds_kind<SL_EPI_F32_GELU, false>(c, xl, panel);
+    case SL_EPI_I8_GELU:
+        return yt ? panel_lds_kind<SL_EPI_I8_GELU, true>(c, xl, panel)
+                  : panel_lds_kind<SL_EPI_I8_GELU, false>(c, xl, panel);
+    default:  // SL_EPI_I8, and with erf
+        return yt ? panel_lds_kind<SL_EPI_I8, true>(c, xl, panel) : panel_lds_kind<SL_EPI_I8, false>(c, xl, panel);
     }
 }
 

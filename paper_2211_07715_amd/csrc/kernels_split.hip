@@ -53,6 +53,8 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
     // then the GELU table
     i32x4 *part = reinterpret_cast<i32x4 *>(smem);
     GeluCell *tab = reinterpret_cast<GeluCell *>(smem + kw * NT * ST * 1024);
+    // (rows at whole words change lanes there before this wave's sums go there)
+    int8_t *const scratch = smem + wave * NT * ST * 1024;
     // this wave's windows: w_j = wave + j * kw, j < nw
     const int nw = wave < a.n_win ? (a.n_win - 1 - wave) / kw + 1 : 0;
 
@@ -67,7 +69,7 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
     // bytes that meet zero weights).
     uint32_t ro[ST];
 #pragma unroll
-    for (int s = 0; s < ST; ++s) ro[s] = src.offset(a, t0 + s * 16 + (lane & 15), lane >> 4);
+    for (int s = 0; s < ST; ++s) ro[s] = src.offset(a, t0 + s * 16 + src.load_token(lane), src.load_group(lane));
 
     RowPiece<XL> bv[WPW][ST];
     i32x4 av[WPW][NT][2];
@@ -123,7 +125,7 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
             for (int h = 0; h < 2; ++h) {
                 i32x4 rows[ST];
 #pragma unroll
-                for (int s = 0; s < ST; ++s) rows[s] = src.aligned(bv[j][s], h, ro[s]);
+                for (int s = 0; s < ST; ++s) rows[s] = src.operand(bv[j][s], h, ro[s], scratch, lane);
 #pragma unroll
                 for (int c = 0; c < NT; ++c)
 #pragma unroll

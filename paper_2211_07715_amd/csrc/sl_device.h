@@ -120,7 +120,8 @@ struct RowPiece<RowsAt::kBytes> {
     int last[2];
 };
 
-template <RowsAt XL>
+// REGROUP: see operand().
+template <RowsAt XL, bool REGROUP = XL == RowsAt::kWords>
 struct RowSource {
     static constexpr bool XT = XL == RowsAt::kBlocks;
     static constexpr uint32_t kHalf = XT ? 2 * 512 : 64;      // bytes to the second half of a window
@@ -163,9 +164,26 @@ struct RowSource {
         }
         return p;
     }
-    __device__ __forceinline__ i32x4 aligned(const RowPiece<XL> &p, int h, uint32_t off) const
+    // The B operand of half h: lane l holds features 16 (l / 16) .. of token
+    // l % 16. Rows at whole words can be loaded by other lanes, token l / 4 and
+    // features 16 (l % 4) .., with REGROUP, so that four lanes in a row read 64 contiguous
+    // bytes (an instruction that reads 16 bytes of another row in each lane
+    // runs at a quarter of the address unit's rate), and change places through
+    // 1 KiB of LDS of the wave's own (`scratch`; a wave's LDS operations take
+    // effect in order). The pieces of token t are permuted by bits 2 and 3 of
+    // t, so that neither side meets a bank twice.
+    static constexpr bool kRegroup = REGROUP;
+    static_assert(!REGROUP || XL == RowsAt::kWords, "blocks need none; rows at any byte shift by their own token");
+    static constexpr int kScratch = kRegroup ? 1024 : 0;
+    __device__ __forceinline__ static int load_token(int lane) { return kRegroup ? lane >> 2 : lane & 15; }
+    __device__ __forceinline__ static int load_group(int lane) { return kRegroup ? lane & 3 : lane >> 4; }
+    __device__ __forceinline__ i32x4 operand(const RowPiece<XL> &p, int h, uint32_t off, int8_t *scratch, int lane) const
     {
-        if constexpr (XL == RowsAt::kBytes) {
+        if constexpr (kRegroup) {
+            *reinterpret_cast<i32x4 *>(scratch + (lane ^ ((lane >> 4) & 3)) * 16) = p.v[h];
+            const int t = lane & 15;
+            return *reinterpret_cast<const i32x4 *>(scratch + (t * 4 + ((lane >> 4) ^ (t >> 2))) * 16);
+        } else if constexpr (XL == RowsAt::kBytes) {
             i32x4 r;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
@@ -494,7 +512,7 @@ struct PanelCfg {
 constexpr int kNumPanelCfgs = 7;
 extern const PanelCfg kPanelCfgs[kNumPanelCfgs];
 // LDS bytes of a panel kernel launch whose panel takes `panel` bytes
-size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, bool yt, uint64_t panel);
+size_t panel_lds_bytes(PanelCfg c, int32_t run_kind, RowsAt xl, bool yt, uint64_t panel);
 sl_status launch_panel(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, PanelCfg c, RowsAt xl, bool yt,
                        size_t lds, hipStream_t stream);
 // The shapes that also come for RowsAt::kBytes: the widest and the narrowest
