@@ -6,7 +6,9 @@
 // the dense input ("re-organised"), products accumulate in int32, and bias and
 // the other post-operators are applied once per output before the store.
 //
-// MI355X mapping:
+// MI355X mapping of the kernel in this file, the staged kernel (the others,
+// which run for most sizes, multiply dense operands; kernels_panel.hip says
+// why):
 //  * The weight operand is the A operand of v_smfmac_i32_16x16x128_i8, the
 //    4:2-sparse int8 matrix-core instruction: 16 output channels (4
 //    block-rows) x one 128-column window, at most 2 stored values per row in

@@ -511,7 +511,7 @@ static sl_status launch_panel_cfg(const LinearArgs &a, const GeluArg *ep, size_t
     F(4, 2, 8, 2)          \
     F(2, 2, 8, 4)          \
     F(2, 4, 4, 2)          \
-    F(8, 2, 8, 2)         \
+    F(8, 2, 8, 2)          \
     F(8, 2, 12, 2)
 
 const PanelCfg kPanelCfgs[kNumPanelCfgs] = {
