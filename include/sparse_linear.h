@@ -101,7 +101,9 @@ typedef struct sl_packed_weight sl_packed_weight;
  *   out           receives the handle; *out is set to NULL on failure.
  * Copies everything it needs (the caller keeps ownership of its buffers),
  * allocates device memory with hipMalloc and synchronises the upload.
- * Returns SL_ERR_UNSUPPORTED when the current device is not gfx950.
+ * Returns SL_ERR_UNSUPPORTED when the current device is not gfx950, or when
+ * the 4:2 operand image (1088 bytes a 16-channel x 128-column tile; n_out x
+ * k_in of about 4.0e9) or its overflow operands pass 2 GiB.
  */
 sl_status sparse_linear_pack(const int8_t *w_host, int32_t n_out, int32_t k_in, int32_t block_h,
                              int32_t block_w, const float *w_scale_host, const float *bias_host,

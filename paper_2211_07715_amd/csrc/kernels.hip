@@ -676,12 +676,14 @@ sl_status upload_image(sl_packed_weight *w)
                 om[((size_t)wi * ncg + g) * 2 + 1] = pp[0];
             }
     }
-    // the dense operand image, from the canonical blocks
+    // The dense operand image, from the canonical blocks. It may pass 2 GiB: an
+    // operand takes 2048 bytes here and 1088 in the main image, whose size is
+    // limited above, so every byte of it (and the operands of up to 8 tiles
+    // past it that a ragged last channel group asks for, which read as zeros)
+    // has an offset below 2^32, as the buffer loads need.
+    static_assert((uint64_t)kMaxBufferBytes / kOpBytes * kDenseOp + 8 * kDenseOp < (1ull << 32),
+                  "32-bit offsets reach every operand");
     const uint64_t dense_bytes = (uint64_t)ti.n_win * ti.n_tiles * kDenseOp;
-    if (dense_bytes > (uint64_t)kMaxBufferBytes) {
-        set_error("packed weight image over 2 GiB (n_out x k_in too large for one image)");
-        return SL_ERR_UNSUPPORTED;
-    }
     std::vector<int8_t> dense((size_t)dense_bytes, 0);
     for (int32_t g = 0; g < w->n_out / 4; ++g)
         for (uint32_t e = w->row_ptr[g]; e < w->row_ptr[g + 1]; ++e) {

@@ -81,7 +81,8 @@ __device__ __forceinline__ void split_body(const LinearArgs &a, const GeluArg *e
             for (int s = 0; s < ST; ++s) bv[j][s] = src.load(ro[s], (int)w);
 #pragma unroll
             for (int c = 0; c < NT; ++c) {
-                const uint32_t base = c < ntl ? (uint32_t)(tile0 + c) * kDenseOp + 16u * (uint32_t)lane : kOob;
+                // (a tile past the last one reads the last one's: its sums are not used)
+                const uint32_t base = (uint32_t)(tile0 + min(c, ntl - 1)) * kDenseOp + 16u * (uint32_t)lane;
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                     av[j][c][h] = __builtin_bit_cast(

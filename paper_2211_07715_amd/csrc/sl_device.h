@@ -42,11 +42,12 @@ __device__ __forceinline__ void store_nt_at4(void *p, i32x4 v)
 
 constexpr int kXcds = 8;  // accelerator complex dies, each with its own L2
 constexpr int kMaxDevices = 64;
-// Buffer-load offset past any buffer this library reads (all < 2 GiB): such
-// a lane reads zeros. Buffer word 3 for raw byte loads on gfx9.
+// Buffer-load offset past any buffer of token rows, scales, biases or 4:2
+// operands (all < 2 GiB; the dense operand image may be larger): such a lane
+// reads zeros. Buffer word 3 for raw byte loads on gfx9.
 constexpr uint32_t kOob = 0x80000000u;
 constexpr int32_t kRsrcWord3 = 0x00020000;
-constexpr int64_t kMaxBufferBytes = 0x7ff00000;  // per launch: token chunk bytes and weight image
+constexpr int64_t kMaxBufferBytes = 0x7ff00000;  // per launch: token chunk bytes and 4:2 weight images
 constexpr int kVecLds = 512;  // a compute wave's weight scales and biases (staged kernel)
 constexpr int kGeluLds = (kGeluCells * (int)sizeof(GeluCell) + 15) / 16 * 16;
 constexpr int kMaskLds = 256;  // the ring buffers' overflow masks
