@@ -215,6 +215,15 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
         });
     };
 
+    // Int8 epilogues whose temporaries of two fragments do not fit beside the
+    // accumulators finish one fragment before the next begins: erf's, and the
+    // table's in the 168 registers of 12 waves with 8 tiles or with row
+    // addresses. Left to the scheduler they spilled 28 to 200 bytes a lane; us,
+    // two fragments -> one: erf, FFN1 768 -> 3072 in blocks at 4096 / 49152
+    // tokens 26.7 -> 20.6 / 228 -> 211; table, 1024 -> 4096 in blocks at 2048 /
+    // 4096 / 49152 tokens 18.8 -> 15.0 / 25.3 -> 22.8 / 198 -> 183.
+    constexpr bool kOneFragment =
+        KIND == kEpiI8GeluErf || (KIND == SL_EPI_I8_GELU && NWV == 12 && (NT == 8 || !YT));
     // accumulator layout: lane l holds rows 4*(l/16)+r (channels of one
     // block-row), column l%16 (token), r = 0..3
     auto scales = [&](int c, float (&s)[4], float (&bb4)[4]) {
@@ -254,14 +263,15 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
                     constexpr bool Q = decltype(two)::value;
                     uint32_t v[4];
                     // (two fragments at a time: the GELU kind's table reads
-                    // of 8 outputs a lane are in flight together)
+                    // of 8 outputs a lane are in flight together; one at a
+                    // time where two do not fit in registers)
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const int ca = C0 + (Q ? 0 : 2 * h), sa = S0 + (Q ? h : 0);
                         float s0[4], b0[4], s1[4], b1[4];
                         scales(ca, s0, b0);
                         scales(ca + 1, s1, b1);
-                        if constexpr (KIND == SL_EPI_I8_GELU) {
+                        if constexpr (KIND == SL_EPI_I8_GELU && !kOneFragment) {
                             float gy[2][4];
                             uint32_t ad[2][4];
                             u32x2 cell[2][4];
@@ -275,7 +285,9 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
                             v[2 * h + 1] = gelu_codes(gy[1], cell[1]);
                         } else {
                             v[2 * h] = epilogue_value<KIND>(a, acc[ca][sa], s0, b0, tab, hinv, eoff, cmax);
+                            if constexpr (kOneFragment) __builtin_amdgcn_sched_barrier(0);
                             v[2 * h + 1] = epilogue_value<KIND>(a, acc[ca + 1][sa], s1, b1, tab, hinv, eoff, cmax);
+                            if constexpr (kOneFragment) __builtin_amdgcn_sched_barrier(0);
                         }
                     }
                     transpose4(v);
