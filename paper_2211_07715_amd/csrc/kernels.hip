@@ -981,7 +981,22 @@ static void set_panel_slices(LinearArgs &a, PanelCfg c, int64_t n_cg, int64_t wa
 // address unit's rate, and idle waves count less (QKV at 384 tokens in rows:
 // 4-tile groups 5.3 us, 2-tile groups, which read the rows twice as often,
 // 8.1). SL_PTILE="nt,st,nwv,r" overrides the shape and SL_PSLICES=n the number
-// of token slices (tests: many token groups a wave at small sizes). Where that picks 6-tile groups, an 8-tile shape takes their place
+// of token slices (tests: many token groups a wave at small sizes).
+// From row-major X another width takes the place of the one it picks if one
+// workgroup a CU then has few token groups (us):
+//  * outputs of 4 bytes: 4-tile groups that of 6-tile ones, and with GELU 2-tile
+//    groups that of wider ones, at most one token group a wave: a wave's chain
+//    is the shorter (6 -> 4 tiles: 1024 -> 4096 at 700 / 1024 tokens, fp32 10.0
+//    -> 8.4 / 10.7 -> 9.3, with GELU 14.2 -> 11.2 / 15.2 -> 12.1; with two groups
+//    a wave, 768 -> 3072 at 1536, 9.4 -> 10.2; GELU, 4 -> 2 tiles: 1024 -> 3072
+//    at 255 / 512 9.5 -> 7.5 / 9.8 -> 9.0; without GELU at 512 7.5 -> 7.7);
+//  * int8 outputs, whose rows are not regrouped: 4-tile groups that of 6- and of
+//    2-tile ones, at most 4 token groups, and into blocks over at most 4 windows
+//    8 (GELU: 512 -> 2048 at 384, 2 -> 4 tiles, 6.7 -> 5.8; 128 -> 624 at 1700,
+//    3 groups, 7.4 -> 5.7; into blocks 96 -> 2400 at 1400, 8 groups, 6.5 -> 5.2;
+//    768 -> 3072 at 1024, 7 groups, into rows and blocks 9 and 13 % slower; 2 -> 4
+//    tiles over one window, 36 -> 180 at 5322, 5.8 -> 6.1).
+// Where it stays with 6-tile groups, an 8-tile shape takes their place
 //  * for int8 outputs in rows: its 128 channels are whole cache lines of Y,
 //    where 96 leave every line to two workgroups (4096 / 49152 tokens, us:
 //    QKV 15.5 -> 13.5 / 136 -> 104, FFN1 21.0 -> 18.4 / 175 -> 140, BERT-large
@@ -989,7 +1004,11 @@ static void set_panel_slices(LinearArgs &a, PanelCfg c, int64_t n_cg, int64_t wa
 //  * elsewhere, if each SIMD then has less work by over 8 % (the channels
 //    leave a remainder of 6 tiles that 8 divide: BERT-large FFN1 in blocks at
 //    49152 tokens 212 -> 195 us with 17 % less work; with equal work the two
-//    shapes measure within 4 % of each other either way).
+//    shapes measure within 4 % of each other either way). Outputs of 4 bytes
+//    keep 6 tiles where no wave has a second token group, and so 8 tiles the
+//    longer chain (1024 -> 4096 rows at 700 tokens, fp32 10.0 against 11.6 us,
+//    with GELU 14.2 against 16.6; at 1537, two groups of 6 tiles or one of 8,
+//    16.1 against 14.8).
 // Fills a's channel-group and slice fields; SL_ERR_UNSUPPORTED when no panel
 // fits.
 static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int32_t run_kind, RowsAt xl, bool yt,
@@ -1064,6 +1083,24 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
     }
     if (!found) return SL_ERR_UNSUPPORTED;
     const bool i8 = run_kind != SL_EPI_ACC_I32 && run_kind != SL_EPI_F32 && run_kind != SL_EPI_F32_GELU;
+    if (!have_forced && xl == RowsAt::kWords && env_cfg().pslices == 0)
+        for (const PanelCfg c : {PanelCfg{2, 2, 8, 4}, PanelCfg{4, 2, 8, 2}}) {
+            const bool takes = c.nt == 2 ? run_kind == SL_EPI_F32_GELU && out->nt > 2
+                                         : out->nt == 6 || (i8 && out->nt == 2 && ti.n_win > 1);
+            if (!takes) continue;
+            const int64_t most = !i8 || (yt && ti.n_win <= 4) ? c.nwv : 4;
+            const int64_t n_cg = (ti.n_tiles + c.nt - 1) / c.nt;
+            const size_t lds = panel_lds_bytes(c, run_kind, xl, yt, (uint64_t)ti.n_win * c.nt * kDenseOp);
+            LinearArgs t = a;
+            set_panel_slices(t, c, n_cg, std::max<int64_t>(1, n_cu / n_cg));
+            if (lds > kLdsMax || t.slice_groups > most || n_cg * t.n_slices > n_cu) continue;
+            *out = c;
+            *lds_out = lds;
+            a.n_cgroups = t.n_cgroups;
+            a.n_slices = t.n_slices;
+            a.slice_groups = t.slice_groups;
+            break;
+        }
     if (!have_forced && out->nt == 6 && w->n_out > 96 && env_cfg().pslices == 0) {
         const bool lines = i8 && !yt;
         // (erf's temporaries spill in the registers of 12 waves: 1024 -> 4096 in
@@ -1075,7 +1112,8 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
         set_panel_slices(t, c8, n_cg, std::max<int64_t>(1, n_cu / n_cg));
         // tile products of the busiest SIMD (a workgroup's groups go round its SIMDs)
         const auto work = [](const LinearArgs &l, PanelCfg c) { return (l.slice_groups + 3) / 4 * c.nt * c.st; };
-        if (lds <= kLdsMax && (lines || work(t, c8) * 100 < work(a, *out) * 92)) {
+        const bool keep6 = !i8 && a.slice_groups <= out->nwv;
+        if (lds <= kLdsMax && (lines || (!keep6 && work(t, c8) * 100 < work(a, *out) * 92))) {
             *out = c8;
             *lds_out = lds;
             a.n_cgroups = t.n_cgroups;

@@ -50,7 +50,16 @@ def test_wide_shapes(hip, monkeypatch, shape, m, n, k):
 @pytest.mark.parametrize("n,k,m,kind,blocks,want", [
     (2304, 768, 4096, 3, False, "panel 8,2,8,2"), (2308, 768, 4096, 1, False, "panel 6,2"),
     (4096, 1024, 8192, 3, True, "panel 8,2,12,2"), (3072, 768, 4096, 3, True, "panel 6,2,12,2"),
-    (768, 768, 4096, 3, True, "panel"), (768, 768, 4096, 1, False, "panel")])
+    (768, 768, 4096, 3, True, "panel"), (768, 768, 4096, 1, False, "panel"),
+    # one token group a wave of the 4-tile shape, or of the 2-tile one with GELU,
+    # from rows; a wave's second group of 6 tiles against its first of 8
+    (4096, 1024, 700, 1, False, "panel 4,2,8,2"), (4096, 1024, 1000, 2, False, "panel 4,2,8,2"),
+    (3072, 1024, 255, 2, False, "panel 2,2,8,4"), (3072, 1024, 700, 2, False, "panel 4,2,8,2"),
+    (3072, 1024, 255, 1, False, "panel 4,2,8,2"), (3072, 768, 1500, 1, False, "panel 6,2"),
+    (4096, 1024, 1537, 1, False, "panel 8,2,12,2"), (3072, 768, 2228, 2, True, "panel 8,2,12,2"),
+    # int8 from rows: few token groups, or a short reduction into blocks
+    (2048, 512, 384, 4, False, "panel 4,2,8,2"), (624, 128, 1700, 4, False, "panel 4,2,8,2"),
+    (2400, 96, 1400, 4, False, "panel 8,2,8,2"), (3072, 768, 1024, 3, False, "panel 8,2,8,2")])
 def test_wide_choice(hip, monkeypatch, n, k, m, kind, blocks, want):
     import torch
     monkeypatch.delenv("SL_PATH", raising=False)
@@ -62,9 +71,10 @@ def test_wide_choice(hip, monkeypatch, n, k, m, kind, blocks, want):
     xl = T if blocks else 0
     xd = torch.from_numpy(np.ascontiguousarray(hip.to_t16x32(x)) if blocks else x).cuda()
     so, ref = _refs(np.ascontiguousarray(x[rows]), w, sw, b)[kind]
-    y = pw.run(xd, 0.02, kind, out_scale=so, x_layout=xl, y_layout=xl, m_tokens=m)
+    yl = xl if kind in (3, 4) else 0
+    y = pw.run(xd, 0.02, kind, out_scale=so, x_layout=xl, y_layout=yl, m_tokens=m)
     torch.cuda.synchronize()
     assert hip.last_path().startswith(want), hip.last_path()
-    got = hip.from_t16x32(y.cpu().numpy(), m, n) if blocks else y.cpu().numpy()
+    got = hip.from_t16x32(y.cpu().numpy(), m, n) if yl else y.cpu().numpy()
     check(kind, got[rows], ref, f"{n}x{k} m={m} {hip.last_path()}")
     pw.free()
