@@ -929,21 +929,33 @@ static bool one_full_round(bool direct, int64_t m, const sl_packed_weight *w)
 }
 
 // Channel tiles of the tile kernel's workgroups for a launch, or 0 where
-// another kernel runs. Of 6 and 8 tiles the one whose workgroups need less
-// time by rounds of the CUs times the operand bytes of a window (128 tokens
-// and 16 channels a tile; 4096 tokens, fp32 rows, us: 768x3072 6 tiles 16.4, 8
-// tiles 17.7, 1024x4096 34.5 and 22.8).
-//  * From row-major X, and for int8 rows of Y: where its 6-tile workgroups
-//    would fill over half of the CUs (768x3072, us, against the staged or
-//    direct kernel: 2900 tokens 22.7 -> 15.4, 4096 18.3 -> 16.4, 49152 176 ->
-//    148, int8 20.2 -> 15.5 and 187 -> 141, int8 from blocks 156 -> 139; at
-//    2048, 128 workgroups, 14.1 against 14.6).
-//  * From block-layout X the direct kernel loads half the operands past LDS
-//    and is faster per round: only where the 8-tile workgroups take less than
-//    0.83 of its time by that count (1024x4096 at 4096 / 49152 tokens 30.1 ->
-//    23.0 / 262 -> 250; 768x3072 at 49152, 0.86 by that count: 141 and 148).
-static int choose_tile_nt(const char *path, bool auto_path, bool xt, bool yt, int64_t out_bytes, int64_t m,
-                          const sl_packed_weight *w)
+// another kernel runs. Times are counted in operand rows and columns: rounds of
+// the CUs, times a window's 128 tokens and 16 channels a tile (1.9 ns each),
+// plus what finishing a tile takes, which nothing overlaps here while the
+// persistent kernels (staged, direct: 128 x 96 items) overlap most of it. The
+// constants are fitted to 2600 calls of 1024 to 49152 tokens, 640 to 4096
+// channels and 1040 to 4096 columns. Of 1479 drawn others, counting it moves 203,
+// which get 7 % faster as a whole (11 of them 4 to 10 % slower).
+//  * Int8 rows of Y: where the other kernels' 64 x 96 items make more than one
+//    round of the CUs (768x3072, us, against them: 4096 tokens 20.2 -> 15.5,
+//    49152 187 -> 141, from blocks 156 -> 139; 4096 channels from 1040 columns at
+//    49152 471 -> 446): they store 4 bytes a lane.
+//  * Outputs of 4 bytes from row-major X: the same, up to two rounds (768x3072
+//    fp32, against the staged kernel: 2900 tokens 22.7 -> 15.4, 4096 18.3 ->
+//    16.4; at 2048, 128 workgroups, 14.1 against 14.6). Past that long
+//    reductions, where windows outweigh finishing, the more so the wider the
+//    rows of Y (768x3072 at 49152 176 -> 148; 4096 channels at 8192 tokens: 1408
+//    columns 80 against 110 here, 4096 columns 59 against 43 at 1024 channels).
+//  * Int8 blocks from row-major X, against the direct kernel: the same in one
+//    round, past it likewise; rows whose width is no multiple of 128 load a
+//    fifth faster into its registers (1024 channels at 20000 tokens: 1152
+//    columns 51 -> 45, 1168 columns 46 against 50 here).
+//  * From block-layout X the direct kernel loads half the operands past LDS and
+//    is faster per round: 8-tile workgroups where they need fewer rounds and
+//    windows outweigh finishing (1024x4096 at 4096 / 49152 tokens 30.1 -> 23.0 /
+//    262 -> 250; fp32, 4096 channels from 1040 columns at 4096 33 against 47).
+static int choose_tile_nt(const char *path, bool auto_path, bool xt, bool yt, int32_t run_kind, int64_t out_bytes,
+                          int64_t m, const sl_packed_weight *w)
 {
     const bool forced = strcmp(path, "tile") == 0;
     if (!forced && !(auto_path && w->tiles.n_win > kPanelMaxWin)) return 0;
@@ -954,12 +966,25 @@ static int choose_tile_nt(const char *path, bool auto_path, bool xt, bool yt, in
     const auto items = [&](int nt) {
         return (m + kTileTokens - 1) / kTileTokens * ((w->tiles.n_tiles + nt - 1) / nt);
     };
-    const auto time = [&](int nt) { return (items(nt) + n_cu - 1) / n_cu * (kTileTokens + 16 * nt); };
+    const auto rounds = [&](int nt) { return (items(nt) + n_cu - 1) / n_cu; };
+    const int64_t n_win = w->tiles.n_win, n = w->n_out;
+    const auto time = [&](int nt, int64_t finish) {
+        return rounds(nt) * (n_win * (kTileTokens + 16 * nt) + finish);
+    };
+    const auto other = [&](int64_t window, int64_t finish) { return rounds(6) * (n_win * window + finish); };
     if (forced && env_cfg().tile[0] > 0) return env_cfg().tile[0] == 8 ? 8 : 6;
-    const int nt = time(8) < time(6) ? 8 : 6;
-    if (forced || ((!xt || (out_bytes == 1 && !yt)) && items(6) * 2 > n_cu)) return nt;
-    // (the direct kernel's items are 128 tokens x 6 tiles too)
-    return xt && time(8) * 100 < time(6) * 83 ? 8 : 0;
+    const int nt = time(8, 0) < time(6, 0) ? 8 : 6;
+    const bool i8_rows = out_bytes == 1 && !yt;
+    if (forced) return nt;
+    if (xt && !i8_rows) return time(8, 2800) < other(230, 650) ? 8 : 0;
+    if ((m + 63) / 64 * ((w->tiles.n_tiles + 5) / 6) <= n_cu) return 0;
+    if (i8_rows || rounds(nt) <= (out_bytes == 1 ? 1 : 2)) return nt;
+    const bool gelu = run_kind == SL_EPI_F32_GELU;
+    const int64_t finish = out_bytes == 1 ? 1600 + n / 5 : gelu ? 1500 + n * 7 / 10 : 2000 + n * 2 / 5;
+    const int64_t instead = out_bytes == 1 ? other(w->k_in % kWin ? 270 : 346, 400)
+                                           : other(250, gelu ? 2000 : 1200);
+    const int best = time(8, finish) < time(6, finish) ? 8 : 6;
+    return time(best, finish) < instead ? best : 0;
 }
 
 // Token slices of a weight-stationary launch: `want` per channel group.
@@ -1245,7 +1270,7 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
             if (pst != SL_ERR_UNSUPPORTED) return pst;
         }
         // Long reductions (and SL_PATH=tile) over enough tokens: the tile kernel.
-        const int tile_nt = vec ? choose_tile_nt(path, auto_path, xt, yt, out_bytes, a.m, w) : 0;
+        const int tile_nt = vec ? choose_tile_nt(path, auto_path, xt, yt, run_kind, out_bytes, a.m, w) : 0;
         if (tile_nt) {
             a.n_cgroups = (ti.n_tiles + tile_nt - 1) / tile_nt;
             a.n_items = (a.m + kTileTokens - 1) / kTileTokens * a.n_cgroups;

@@ -48,7 +48,15 @@ def test_tile_shapes(hip, monkeypatch, nt, m, n, k):
     (768, 3072, 4096, 1, 0, 0, "tile 128,6"), (768, 3072, 4096, 3, T, 0, "tile 128,6"),
     (768, 3072, 4096, 3, T, T, "direct"), (768, 3072, 4096, 3, 0, T, "tile 128,6"),
     (768, 3072, 2048, 1, 0, 0, "staged"), (1024, 4096, 4096, 1, T, 0, "tile 128,8"),
-    (1024, 4096, 4096, 1, 0, 0, "tile 128,8"), (768, 768, 4096, 1, 0, 0, "panel")])
+    (1024, 4096, 4096, 1, 0, 0, "tile 128,8"), (768, 768, 4096, 1, 0, 0, "panel"),
+    # more rounds of workgroups: short reductions stay with the kernels that
+    # overlap finishing a tile, long ones and int8 rows do not
+    (4096, 1408, 8192, 1, 0, 0, "staged"), (1072, 1184, 11821, 0, 0, 0, "staged"),
+    (4096, 1040, 8192, 2, 0, 0, "staged"), (1072, 1040, 4096, 1, 0, 0, "tile 128,6"),
+    (1024, 4096, 12000, 1, 0, 0, "tile 128,8"), (4096, 1040, 4096, 3, 0, 0, "tile 128,8"),
+    (4096, 1040, 4096, 4, 0, T, "direct"), (1024, 1152, 8192, 4, 0, T, "tile 128,8"),
+    (4096, 1040, 2048, 1, T, 0, "direct"), (4096, 1040, 4096, 3, T, T, "direct"),
+    (4096, 1040, 4096, 3, T, 0, "tile 128,8")])
 def test_tile_choice(hip, monkeypatch, n, k, m, kind, xl, yl, want):
     import torch
     monkeypatch.delenv("SL_PATH", raising=False)
