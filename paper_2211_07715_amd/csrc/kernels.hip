@@ -1271,9 +1271,13 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         }
         // Long reductions (and SL_PATH=tile) over enough tokens: the tile kernel.
         const int tile_nt = vec ? choose_tile_nt(path, auto_path, xt, yt, run_kind, out_bytes, a.m, w) : 0;
-        if (tile_nt) {
-            a.n_cgroups = (ti.n_tiles + tile_nt - 1) / tile_nt;
-            a.n_items = (a.m + kTileTokens - 1) / kTileTokens * a.n_cgroups;
+        const int64_t tile_cgs = tile_nt ? (ti.n_tiles + tile_nt - 1) / tile_nt : 0;
+        const int64_t tile_items = (a.m + kTileTokens - 1) / kTileTokens * tile_cgs;
+        // (one workgroup an item: more than a launch takes stay with the
+        // persistent kernels)
+        if (tile_nt && tile_items <= kTileMaxItems) {
+            a.n_cgroups = (int32_t)tile_cgs;
+            a.n_items = tile_items;
             const sl_status tst =
                 launch_tile(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, tile_nt, xt, yt, s);
             if (tst != SL_OK) return tst;

@@ -78,7 +78,7 @@ __device__ __forceinline__ void tile_body(const LinearArgs &a, const GeluArg *ep
             bias = a.bias[ch];
         }
     }
-    static_assert(kGeluCells <= 512, "one table cell a thread");
+    static_assert(kGeluCells <= kTileThreads, "one table cell a thread");
     if constexpr (KIND == SL_EPI_I8_GELU)
         if (tid < ep->nc) cell = ep->cell[tid];
 
@@ -283,7 +283,7 @@ __device__ __forceinline__ void tile_body(const LinearArgs &a, const GeluArg *ep
     constexpr int PIECES = S::TN * EB / 16;
     int8_t *const y8 = static_cast<int8_t *>(a.y);
     const int64_t mlim = YT ? mpad : a.m;
-    for (int u = tid; u < S::TM * PIECES; u += 512) {
+    for (int u = tid; u < S::TM * PIECES; u += kTileThreads) {
         int r, p;
         if constexpr (YT) {
             // a 512-byte block of 16 tokens after the other
@@ -313,13 +313,13 @@ __device__ __forceinline__ void tile_body(const LinearArgs &a, const GeluArg *ep
 }
 
 template <int KIND, int NT, int D, bool XT, bool YT>
-__global__ __launch_bounds__(512) void sparse_linear_tile_kernel(LinearArgs a)
+__global__ __launch_bounds__(kTileThreads) void sparse_linear_tile_kernel(LinearArgs a)
 {
     tile_body<KIND, NT, D, XT, YT>(a, nullptr);
 }
 
 template <int NT, int D, bool XT, bool YT>
-__global__ __launch_bounds__(512) void sparse_linear_tile_gelu_kernel(LinearArgs a, GeluArg ep)
+__global__ __launch_bounds__(kTileThreads) void sparse_linear_tile_gelu_kernel(LinearArgs a, GeluArg ep)
 {
     tile_body<SL_EPI_I8_GELU, NT, D, XT, YT>(a, &ep);
 }
@@ -348,10 +348,10 @@ static sl_status launch_tile_nt(const LinearArgs &a, const GeluArg *ep, hipStrea
         raised[dev] = 1;
     }
     if constexpr (KIND == SL_EPI_I8_GELU)
-        hipLaunchKernelGGL((sparse_linear_tile_gelu_kernel<NT, D, XT, YT>), dim3((uint32_t)a.n_items), dim3(512), lds,
+        hipLaunchKernelGGL((sparse_linear_tile_gelu_kernel<NT, D, XT, YT>), dim3((uint32_t)a.n_items), dim3(kTileThreads), lds,
                            stream, a, *ep);
     else
-        hipLaunchKernelGGL((sparse_linear_tile_kernel<KIND, NT, D, XT, YT>), dim3((uint32_t)a.n_items), dim3(512), lds,
+        hipLaunchKernelGGL((sparse_linear_tile_kernel<KIND, NT, D, XT, YT>), dim3((uint32_t)a.n_items), dim3(kTileThreads), lds,
                            stream, a);
     HIP_TRY(hipGetLastError());
     return SL_OK;
@@ -377,7 +377,7 @@ static sl_status launch_tile_kind(const LinearArgs &a, const GeluArg *ep, int nt
 sl_status launch_tile(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, int nt, bool xt, bool yt,
                       hipStream_t stream)
 {
-    if (a.n_items < 1 || a.n_items > 0x7fffffff || (nt != 6 && nt != 8)) {
+    if (a.n_items < 1 || a.n_items > kTileMaxItems || (nt != 6 && nt != 8)) {
         set_error("internal: tile launch out of range");
         return SL_ERR_UNSUPPORTED;
     }

@@ -530,6 +530,8 @@ sl_status panel_resident(PanelCfg c, size_t lds, int *out);
 // kTileTokens tokens x nt (6 or 8) 16-channel tiles each; token rows in the
 // block layout or 16-byte aligned.
 constexpr int kTileTokens = 128;
+constexpr int kTileThreads = 512;
+constexpr int64_t kTileMaxItems = 0xffffffffll / kTileThreads;  // a launch has less than 2^32 threads
 sl_status launch_tile(const LinearArgs &a, const GeluArg *ep, int32_t run_kind, int nt, bool xt, bool yt,
                       hipStream_t stream);
 

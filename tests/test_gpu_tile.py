@@ -8,6 +8,7 @@ in test_gpu_parity.py.
 import numpy as np
 import pytest
 
+import oracle
 from test_gpu_panel import T, _refs
 from test_gpu_parity import KINDS, _case, check, say
 
@@ -72,3 +73,33 @@ def test_tile_choice(hip, monkeypatch, n, k, m, kind, xl, yl, want):
     got = hip.from_t16x32(y.cpu().numpy(), m, n) if yl == T else y.cpu().numpy()
     check(kind, got[rows], ref, f"{n}x{k} m={m} {hip.last_path()}")
     pw.free()
+
+
+def test_more_tiles_than_a_launch_takes(hip, monkeypatch):
+    """2,063,872 x 66,720 int8 outputs (137 GB) would be 8.4 million tile
+    workgroups, over the 2^32 threads of one launch: another kernel runs them."""
+    import torch
+    m, n, k = 2063872, 66720, 1040
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GiB of free GPU memory")
+    monkeypatch.delenv("SL_PATH", raising=False)
+    rng = np.random.default_rng(5)
+    w = np.zeros((n // 4, 4, k), np.int8)
+    for _ in range(16):
+        w[np.arange(n // 4), :, rng.integers(0, k, n // 4)] = rng.integers(1, 128, (n // 4, 4), dtype=np.int8)
+    w = w.reshape(n, k)
+    sw = rng.uniform(0.001, 0.01, n).astype(np.float32)
+    pw = hip.PackedWeight.pack(w, sw)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randint(-127, 128, (m, k), dtype=torch.int8, device="cuda", generator=g)
+    say(f"tile launch limit m={m} n={n} k={k}")
+    y = pw.run(x, 0.02, 3, out_scale=0.05)
+    torch.cuda.synchronize()
+    assert not hip.last_path().startswith("tile"), hip.last_path()
+    rows = torch.cat([torch.arange(0, m, m // 40), torch.arange(m - 3, m)]).cuda()
+    got, xs = y[rows].cpu().numpy(), x[rows].cpu().numpy()
+    check(3, got, oracle.linear(xs, w, 0.02, sw, None, 3, so=0.05), f"{n}x{k} m={m} {hip.last_path()}")
+    pw.free()
+    del x, y
+    torch.cuda.empty_cache()
+
