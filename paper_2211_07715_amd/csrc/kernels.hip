@@ -42,6 +42,7 @@
 #include <string>
 #include <type_traits>
 
+#include "resident_table.h"
 #include "sl_device.h"
 
 namespace sl {
@@ -1057,22 +1058,12 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
         const uint64_t panel = (uint64_t)ti.n_win * c.nt * kDenseOp;
         const size_t lds = panel_lds_bytes(c, run_kind, xl, yt, panel);
         if (lds > kLdsMax) continue;
-        // resident workgroups per device, cached per (device, shape, LDS size)
-        static thread_local struct {
-            int dev, ci;
-            size_t lds;
-            int res;
-        } cache[16];
-        static thread_local int cache_n = 0;
-        int res = -1;
-        for (int i = 0; i < cache_n; ++i)
-            if (cache[i].dev == dev && cache[i].ci == ci && cache[i].lds == lds) res = cache[i].res;
-        if (res < 0) {
-            const sl_status st = panel_resident(c, lds, &res);
-            if (st != SL_OK) return st;
-            cache[cache_n % 16] = {dev, ci, lds, res};
-            cache_n = cache_n < 16 ? cache_n + 1 : 16;
-        }
+        // (us a call of a process that has run more than 16 (shape, LDS size)
+        // pairs, 16 kept -> all of them: 8.1 -> 6.2)
+        static ResidentTable<kMaxDevices, kNumPanelCfgs, kLdsMax> resident;
+        int res = 0;
+        const sl_status st = resident.get(dev, ci, lds, &res, [&](int *out_res) { return panel_resident(c, lds, out_res); });
+        if (st != SL_OK) return st;
         if (res < 1) continue;
         const int64_t n_cg = (ti.n_tiles + c.nt - 1) / c.nt;
         // slices: enough workgroups to fill the resident slots once, or one

@@ -81,7 +81,7 @@ struct PLds {
     static constexpr int kTab = KIND == SL_EPI_I8_GELU ? kGeluLds : 0;
     static constexpr int kWave = std::max(panel_transposes<KIND, YT, NT>() ? S::TR : 0, PanelRows<KIND, XL>::kScratch);
     static constexpr int kFixed = S::VEC + kTab + NWV * kWave;
-    static_assert(kFixed % 16 == 0, "the copies write 16-byte pieces");
+    static_assert(kFixed % 256 == 0 && S::WB % 256 == 0, "16-byte copies; the table of resident workgroups");
     static size_t bytes(uint64_t panel) { return (size_t)kFixed + panel; }
 };
 
