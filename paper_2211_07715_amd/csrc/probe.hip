@@ -32,7 +32,9 @@ __global__ __launch_bounds__(256) void probe_copy_kernel(const i32x4 *__restrict
 // iters rounds of 8 independent matrix instructions per wave; every thread
 // writes one word of the results (so nothing is dropped), out has
 // gridDim.x * 256 words. OP: 0 dense 16x16x64, 1 dense 32x32x32, 2 sparse
-// 16x16x128.
+// 16x16x128. The accumulators start at different values: from equal ones the
+// compiler exchanged the registers of the 16x16x64 form in every round, dozens of
+// moves that halved its measured rate (2359 TOPS; without them 4343).
 template <int OP>
 __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, int *out)
 {
@@ -43,14 +45,16 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, int *out)
     int t = 0;
     if constexpr (OP == 1) {
         i32x16 acc[8];
-        for (int i = 0; i < 8; ++i) acc[i] = i32x16{};
+        for (int i = 0; i < 8; ++i) acc[i] = i32x16{} + (lane + i);
+#pragma unroll 1
         for (int it = 0; it < iters; ++it)
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc[i], 0, 0, 0);
         for (int i = 0; i < 8; ++i) t ^= acc[i][0] ^ acc[i][15];
     } else {
         i32x4 acc[8];
-        for (int i = 0; i < 8; ++i) acc[i] = i32x4{};
+        for (int i = 0; i < 8; ++i) acc[i] = i32x4{} + (lane + i);
+#pragma unroll 1
         for (int it = 0; it < iters; ++it)
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
