@@ -23,7 +23,7 @@ CASES = [
     (1, 4, 16, 0.35),
     (33, 100, 272, 0.35),      # ragged channel tile and last window
     (20, 32, 256, 0.0),        # nothing stored: bias only
-    (50, 48, 768, 1.0),        # every window of every tile overflows
+    (50, 48, 768, 1.0),        # every block stored
     (130, 200, 1024, 0.1),
     (300, 96, 768, 0.3),
     (65, 768, 3072, 0.1),      # DistilBERT FFN2 shape
@@ -73,7 +73,7 @@ def test_panel_every_shape_kind_layout(hip, monkeypatch, m, n, k, density):
                 if path.startswith(f"panel {shape} "):
                     ran += 1
     pw.free()
-    # the panel fits for every case but the densest large ones
+    # a 2-tile panel fits up to k = 4096
     assert ran > 0, "the weight-stationary kernel never ran"
 
 
@@ -103,15 +103,16 @@ def test_panel_runs_at_distilbert_ffn_shapes(hip, monkeypatch):
 
 
 def test_default_path_choice(hip, monkeypatch):
-    """Without SL_PATH few tokens (at most 1280 work items of 16 tokens x 32
-    channels) go to the split-reduction kernel; beyond that the
-    weight-stationary kernel runs for short reductions (K <= 1024) of
-    widening layers (DistilBERT QKV and FFN1), of long token slices, or
-    unless the direct kernel's work items make one round of the CUs that
-    keeps most of them busy (not so for the square 768 layer at 1024 or
+    """Raw accumulators from block-layout rows without SL_PATH: few tokens (at
+    most 1280 work items of 16 tokens x 32 channels) go to the split-reduction
+    kernel; beyond that the weight-stationary kernel runs for short reductions
+    (K <= 1024) of widening layers (DistilBERT QKV and FFN1), of long token
+    slices, or unless the direct kernel's work items make one round of the CUs
+    that keeps most of them busy (not so for the square 768 layer at 1024 or
     8192 tokens, or 1024x1024 at 4096); the direct kernel elsewhere: FFN2
-    (K = 3072) and the square attention-output layer at 2048 and 4096
-    tokens."""
+    (K = 3072) and the square attention-output layer at 2048 and 4096 tokens.
+    (The other kinds and layouts: test_gpu_panel_wide.py, test_gpu_tile.py and
+    test_gpu_rows_at.py.)"""
     import torch
     import workloads as wk
     monkeypatch.delenv("SL_PATH", raising=False)
@@ -140,8 +141,8 @@ def test_default_path_choice(hip, monkeypatch):
 
 def test_panel_falls_back_when_no_panel_fits(hip, monkeypatch):
     """A reduction too long for any channel group's panel to fit in LDS
-    (k = 16384: 128 windows, over 270 KB for two tiles) gets no panel image;
-    SL_PATH=panel then runs another kernel, with the same results."""
+    (k = 16384: 128 windows, 512 KB for two tiles): SL_PATH=panel runs another
+    kernel, with the same results."""
     import torch
     m, n, k = 20, 8, 16384
     w, sw, b, rng = _case(n, k, 0.3, 11)
