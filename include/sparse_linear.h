@@ -204,12 +204,15 @@ sl_status sparse_linear_info(const sl_packed_weight *w, int32_t *n_out, int32_t 
 sl_status sparse_linear_export_bsr(const sl_packed_weight *w, uint32_t *row_ptr, uint16_t *col, int8_t *vals);
 
 /*
- * Statistics of the GPU tile image: n_tiles channel tiles of 16 output
- * channels; n_entries = matrix-core instructions issued per 16 tokens over all
- * tiles (one per 128-column window that holds a stored block of the tile, plus
- * one per window where some block-row stores 3 or 4 blocks in one aligned
- * group of 4 columns); n_overflow = the latter; image_bytes = bytes of the
- * device image. Any pointer may be NULL.
+ * Statistics of the 4:2 tile image: n_tiles channel tiles of 16 output
+ * channels; n_entries = the 4:2 matrix-core instructions that its stored blocks
+ * take per 16 tokens over all tiles (one per 128-column window that holds a
+ * stored block of the tile, plus one per window where some block-row stores 3
+ * or 4 blocks in one aligned group of 4 columns); n_overflow = the latter;
+ * image_bytes = bytes of that 4:2 image (operands and overflow prefix counts)
+ * with scales and biases. The device also holds a dense image of n_tiles *
+ * ceil(k_in / 128) * 2048 bytes, which image_bytes does not count. Any pointer
+ * may be NULL.
  */
 sl_status sparse_linear_tile_stats(const sl_packed_weight *w, int32_t *n_tiles, int64_t *n_entries,
                                    int64_t *n_overflow, int64_t *image_bytes);

@@ -73,12 +73,6 @@ struct Shape {
     static_assert(TM % 8 == 0, "token rows are copied 8 at a time");
 };
 
-// Position of 16-byte piece p of staged token row r: p ^ xsw(r). The 16 rows
-// one B read touches then start in 16 distinct 16-byte bank groups (and any
-// 8 consecutive rows in 8), so the reads are free of bank conflicts.
-__device__ __forceinline__ int xsw(int r) { return (r ^ (r >> 3)) & 7; }
-
-
 // VEC: X rows are 16-byte aligned and k % 16 == 0, so token rows are copied
 // to LDS with 16-byte direct loads; otherwise they are staged byte by byte.
 template <int KIND, int ST, int CT, int WM, int WN, int D, bool VEC, bool YT>
@@ -192,7 +186,7 @@ __device__ __forceinline__ void sparse_linear_body(const LinearArgs &a, const Ge
                 const int r = ((i * S::NW + pw) * 64 + lane) / 8;
                 const bool in = r < S::TM && m0 + r < a.m;
                 const uint32_t row = (uint32_t)((m0 + r) * a.k);
-                xoff[i] = in ? row + (uint32_t)(((lane & 7) ^ xsw(r)) * 16) : kOob;
+                xoff[i] = in ? row + (uint32_t)(((lane & 7) ^ row_swizzle(r)) * 16) : kOob;
                 xlim[i] = in ? row + (uint32_t)(a.k - 16) : kOob;
             }
 #pragma unroll
@@ -249,7 +243,7 @@ __device__ __forceinline__ void sparse_linear_body(const LinearArgs &a, const Ge
                     const int r = u / kWin, c = u % kWin;
                     const int64_t tok = m0 + r;
                     const int32_t col = w * kWin + c;
-                    b[r * kWin + (((c >> 4) ^ xsw(r)) << 4) + (c & 15)] =
+                    b[r * kWin + (((c >> 4) ^ row_swizzle(r)) << 4) + (c & 15)] =
                         (tok < a.m && col < a.k) ? a.x[tok * a.k + col] : (int8_t)0;
                 }
             }
@@ -346,8 +340,8 @@ __device__ __forceinline__ void sparse_linear_body(const LinearArgs &a, const Ge
     for (int s = 0; s < ST; ++s) {
         const int r = wm * ST * 16 + s * 16 + (lane & 15);
         const int p0 = 2 * (lane >> 4);
-        brow[s][0] = r * kWin + ((p0 ^ xsw(r)) << 4);
-        brow[s][1] = r * kWin + (((p0 + 1) ^ xsw(r)) << 4);
+        brow[s][0] = r * kWin + ((p0 ^ row_swizzle(r)) << 4);
+        brow[s][1] = r * kWin + (((p0 + 1) ^ row_swizzle(r)) << 4);
     }
     // this lane's index word: block-row (lane%16)/4, lane group lane/16
     const int iword = ((lane & 15) >> 2) * 4 + (lane >> 4);
@@ -818,7 +812,8 @@ static sl_status launch_kind(const LinearArgs &a, const GeluArg *ep, TileCfg c, 
 }
 
 // The staged kernel writes the block layout only for rows the direct kernel
-// cannot load (k_in % 16 != 0 or a misaligned x): int8 kinds without VEC.
+// cannot load (at any byte: k_in % 4 != 0 or x not at a whole word) and whose
+// panel does not fit in LDS: int8 kinds without VEC.
 template <int KIND>
 static sl_status launch_vec(const LinearArgs &a, const GeluArg *ep, TileCfg c, hipStream_t stream, bool vec, bool yt)
 {
@@ -834,39 +829,28 @@ static sl_status launch_vec(const LinearArgs &a, const GeluArg *ep, TileCfg c, h
     return vec ? launch_kind<KIND, true, false>(a, ep, c, stream) : launch_kind<KIND, false, false>(a, ep, c, stream);
 }
 
-// Pick the workgroup shape: among shapes that give every CU a workgroup,
-// the one with the least L2 traffic (token rows re-read once per channel
-// group, the weight image once per token group); SL_TILE="st,ct,wm,wn,d"
-// overrides (tuning; unknown shapes are ignored).
+// The staged kernel's workgroup shape: the largest (which re-reads token rows
+// and weight operands least) that has 240 work items, about one a CU, else the
+// one that has most; SL_TILE="st,ct,wm,wn,d" overrides (tuning; unknown shapes
+// are ignored).
 static TileCfg choose_cfg(int64_t m, const sl_packed_weight *w)
 {
     const int *e = env_cfg().tile;
     if (e[0])
         for (const TileCfg &k : kCfgs)
             if (k.st == e[0] && k.ct == e[1] && k.wm == e[2] && k.wn == e[3] && k.d == e[4]) return k;
-    const int32_t n_tiles = w->tiles.n_tiles;
-    const double xbytes = (double)m * w->k_in;
-    const double wbytes = (double)w->tiles.main.size() + (double)w->tiles.ovf.size();
-    const TileCfg *best = nullptr, *most = nullptr;
-    double best_cost = 0;
-    int64_t most_wg = 0;
-    for (const TileCfg &c : kCfgs) {
+    const TileCfg *most = nullptr;
+    int64_t most_items = 0;
+    for (const TileCfg &c : kCfgs) {  // (larger shapes come first)
         if (c.d != 4 || c.wm * c.wn != 4) continue;
-        const int64_t mt = (m + c.tm() - 1) / c.tm();
-        const int64_t cgs = (n_tiles + c.nt() - 1) / c.nt();
-        const int64_t nwg = mt * cgs;
-        if (nwg > most_wg) {
-            most_wg = nwg;
+        const int64_t items = (m + c.tm() - 1) / c.tm() * ((w->tiles.n_tiles + c.nt() - 1) / c.nt());
+        if (items >= 240) return c;
+        if (items > most_items) {
+            most_items = items;
             most = &c;
         }
-        if (nwg < 240) continue;
-        const double cost = xbytes * cgs + wbytes * mt;
-        if (!best || cost < best_cost) {
-            best = &c;
-            best_cost = cost;
-        }
     }
-    return best ? *best : *most;
+    return *most;
 }
 
 // Direct-kernel shape, by the same rule; SL_DTILE="st,nt,wm,d" overrides.
@@ -876,56 +860,36 @@ static DirectCfg choose_direct_cfg(int64_t m, const sl_packed_weight *w)
     if (e[0])
         for (const DirectCfg &k : kDirectCfgs)
             if (k.st == e[0] && k.nt == e[1] && k.wm == e[2] && k.d == e[3]) return k;
-    const int32_t n_tiles = w->tiles.n_tiles;
-    const double xbytes = (double)m * w->k_in;
-    const double wbytes = (double)w->tiles.main.size() + (double)w->tiles.ovf.size();
-    const DirectCfg *best = nullptr, *most = nullptr;
-    double best_cost = 0;
+    const DirectCfg *most = nullptr;
     int64_t most_items = 0;
-    for (const DirectCfg &c : kDirectCfgs) {
-        const int64_t mt = (m + c.tm() - 1) / c.tm();
-        const int64_t cgs = (n_tiles + c.nt - 1) / c.nt;
-        const int64_t items = mt * cgs;
+    for (const DirectCfg &c : kDirectCfgs) {  // (larger shapes come first)
+        const int64_t items = (m + c.tm() - 1) / c.tm() * ((w->tiles.n_tiles + c.nt - 1) / c.nt);
+        if (items >= 240) return c;
         if (items > most_items) {
             most_items = items;
             most = &c;
         }
-        if (items < 240) continue;
-        const double cost = xbytes * cgs + wbytes * mt;
-        if (!best || cost < best_cost) {
-            best = &c;
-            best_cost = cost;
-        }
     }
-    return best ? *best : *most;
+    return *most;
 }
 
-// The default path takes the weight-stationary kernel only for reductions
-// of at most this many 128-feature windows (K <= 1024).
+// The default path takes the weight-stationary kernel for reductions of at
+// most this many 128-feature windows (K <= 1024), and beyond them only for token
+// rows at any byte.
 constexpr int32_t kPanelMaxWin = 8;
 
-// Whether the work items of the kernel that runs where the weight-stationary
-// one does not (direct, else staged) make one round of the CUs that keeps at
-// least 80 % of them busy. Over short reductions that kernel wins only
-// there: a second round costs a whole item's time again, where the
-// weight-stationary kernel reuses its panel.
-static bool one_full_round(bool direct, int64_t m, const sl_packed_weight *w)
+// Whether the direct kernel's work items make one round of the CUs that keeps
+// at least 80 % of them busy. Over short reductions that kernel is as fast as
+// the weight-stationary one only there: a second round costs a whole item's
+// time again, where the weight-stationary kernel reuses its panel.
+static bool one_full_round(int64_t m, const sl_packed_weight *w)
 {
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
         return true;
-    int64_t tm, nt;
-    if (direct) {
-        const DirectCfg c = choose_direct_cfg(m, w);
-        tm = c.tm();
-        nt = c.nt;
-    } else {
-        const TileCfg c = choose_cfg(m, w);
-        tm = c.tm();
-        nt = c.nt();
-    }
-    const int64_t items = (m + tm - 1) / tm * ((w->tiles.n_tiles + nt - 1) / nt);
+    const DirectCfg c = choose_direct_cfg(m, w);
+    const int64_t items = (m + c.tm() - 1) / c.tm() * ((w->tiles.n_tiles + c.nt - 1) / c.nt);
     return items <= n_cu && items * 5 >= (int64_t)n_cu * 4;
 }
 
@@ -1075,7 +1039,9 @@ static sl_status choose_panel_cfg(LinearArgs &a, const sl_packed_weight *w, int3
             set_panel_slices(t, c, n_cg, want);
             const int64_t nwg = n_cg * t.n_slices;
             if (nwg > 0x7fffffff) continue;
-            // busy CUs and the bytes each reads
+            // busy CUs and the bytes each reads (whole rounds of the CUs counted
+            // from row-major X: FFN1 at 384 tokens 8.9 -> 6.5 us; from blocks that
+            // changes none of 800 drawn calls)
             double cus = (double)std::min<int64_t>(n_cu, nwg);
             if (xl != RowsAt::kBlocks) cus = (double)nwg / (double)((nwg + n_cu - 1) / n_cu);
             const double bytes = (xl == RowsAt::kBlocks ? 1.0 : 3.0) * (double)a.m * w->k_in * n_cg + (double)nwg * (double)panel;
@@ -1205,24 +1171,25 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
         const bool vec = xt || ((w->k_in % 16 == 0) && ((reinterpret_cast<uintptr_t>(a.x) & 15) == 0));
         const bool words = xt || ((w->k_in % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.x) & 3) == 0));
         const RowsAt xl = xt ? RowsAt::kBlocks : words ? RowsAt::kWords : RowsAt::kBytes;
-        // Aligned or block-layout rows: the weight-stationary kernel for short
-        // reductions (at most kPanelMaxWin windows), with the shape the cost
-        // model picks (768x768 at 2048 / 4096 tokens, us, against the kernel
-        // it replaced there: int8 blocks 6.2 -> 5.7 / 7.4 -> 6.0, int8 rows
-        // 8.0 -> 6.5 / 10.3 -> 7.7, fp32 rows 7.1 -> 6.2 / 9.2 -> 7.8). Raw
-        // accumulators of block-layout rows take it only for a widening layer
-        // (N > K), slices of at least four token groups a wave, or work items
-        // of the direct kernel that would not make one round of the CUs: else
-        // that kernel is as fast (768x768 at 4096 tokens, 6.8 us both). Longer
-        // reductions: the direct-operand kernel (block-layout input, or
-        // block-layout output from aligned rows) or the staged kernel
-        // (row-major input and output). SL_PATH=panel|direct|staged forces a
-        // kernel (tests, tuning; panel falls back when no panel fits).
-        // Before all of them, few tokens (at most kSplitAutoItems work items
-        // of the split-reduction kernel, about five per compute unit) go to
-        // that kernel (SL_PATH=split forces it): there the other kernels'
-        // work items would not fill the chip and each walks its whole
-        // reduction in series.
+        // Few tokens (at most kSplitAutoItems work items of the split-reduction
+        // kernel, about five per compute unit) go to that kernel: there the
+        // other kernels' work items would not fill the chip and each walks its
+        // whole reduction in series.
+        // Else the weight-stationary kernel for short reductions (at most
+        // kPanelMaxWin windows), with the shape the cost model picks (768x768 at
+        // 2048 / 4096 tokens, us, against the kernel it replaced there: int8
+        // blocks 6.2 -> 5.7 / 7.4 -> 6.0, int8 rows 8.0 -> 6.5 / 10.3 -> 7.7, fp32
+        // rows 7.1 -> 6.2 / 9.2 -> 7.8). Raw accumulators of block-layout rows
+        // take it only for a widening layer (N > K), slices of at least four
+        // token groups a wave, or work items of the direct kernel that would not
+        // make one round of the CUs: else that kernel is as fast (768x768 at 4096
+        // tokens, 6.8 us both).
+        // Longer reductions: the tile kernel where choose_tile_nt says so, else
+        // the direct-operand kernel (block-layout input, rows at whole words that
+        // are not 16-byte aligned, or block-layout output from rows) or the
+        // staged kernel (16-byte aligned row-major input and row-major output).
+        // SL_PATH=split|panel|tile|direct|staged forces a kernel where it can run
+        // (tests, tuning; panel falls back when no panel fits).
         const char *path = env_cfg().path;
         const bool force_split = strcmp(path, "split") == 0;
         const int split_wpw = split_windows_per_wave(ti.n_win);
@@ -1249,7 +1216,7 @@ sl_status launch_linear(const sl_packed_weight *w, const int8_t *x, int32_t x_la
             size_t lds = 0;
             sl_status pst = choose_panel_cfg(a, w, run_kind, xl, yt, &pc, &lds);
             if (pst == SL_OK && !force_panel && xt && kind == SL_EPI_ACC_I32 &&
-                !(w->n_out > w->k_in || a.slice_groups >= 4 * pc.nwv || !one_full_round(direct, a.m, w)))
+                !(w->n_out > w->k_in || a.slice_groups >= 4 * pc.nwv || !one_full_round(a.m, w)))
                 pst = SL_ERR_UNSUPPORTED;
             if (pst == SL_OK) {
                 pst = launch_panel(a, run_kind == SL_EPI_I8_GELU ? &ga : nullptr, run_kind, pc, xl, yt, lds, s);

@@ -103,7 +103,6 @@ __device__ __forceinline__ void static_for(F &&f)
 template <int KIND, int NT, int ST, int NWV, int R, RowsAt XL, bool YT>
 __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *ep)
 {
-    constexpr bool XT = XL == RowsAt::kBlocks, UA = XL == RowsAt::kBytes;
     using S = PShape<NT, ST, NWV>;
     using L = PLds<KIND, NT, ST, NWV, XL, YT>;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
@@ -148,7 +147,6 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
     }
 
     float hinv = 0.0f, eoff = 0.0f, cmax = 0.0f;  // GELU table parameters (set-up below)
-
 
     // ---- token groups of this workgroup's slice, one wave each at a time
     const int64_t mpad = (a.m + 15) / 16 * 16;
@@ -431,7 +429,7 @@ __device__ __forceinline__ void panel_body(const LinearArgs &a, const GeluArg *e
 #pragma unroll
         for (int j = 0; j < LA; ++j) read_unit(ring[j], wbase(0), j);
     }
-        for (int i = 0; i < n_my; ++i) {
+    for (int i = 0; i < n_my; ++i) {
         const int64_t t0 = group_t0(i);
         const bool has_next = i + 1 < n_my;
         row_offsets(has_next ? group_t0(i + 1) : mpad, ron);

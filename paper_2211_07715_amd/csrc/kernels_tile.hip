@@ -41,10 +41,6 @@ struct TShape {
     static_assert(TM * (P4 + P1) <= RING, "the finished tile takes the ring's place");
 };
 
-// bits of the row index that permute the 16-byte pieces of a staged row, so
-// that the 16 rows of a B operand read start in 16 different bank groups
-__device__ __forceinline__ int row_swizzle(int r) { return (r ^ (r >> 3)) & 7; }
-
 template <int KIND, int NT, int D, bool XT, bool YT>
 __device__ __forceinline__ void tile_body(const LinearArgs &a, const GeluArg *ep)
 {

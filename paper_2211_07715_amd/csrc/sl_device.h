@@ -99,6 +99,12 @@ __device__ __forceinline__ int64_t t16x32_offset(int64_t t, int32_t c, int32_t c
     return ((t >> 4) * cb + (c >> 5)) * 512 + (t & 15) * 32 + (c & 31);
 }
 
+// Position of 16-byte piece p of token row r in LDS (staged and tile kernels):
+// p ^ row_swizzle(r). The 16 rows one B operand read touches then start in 16
+// different 16-byte bank groups (and any 8 consecutive rows in 8), so the reads
+// are free of bank conflicts.
+__device__ __forceinline__ int row_swizzle(int r) { return (r ^ (r >> 3)) & 7; }
+
 // Where the token rows of X lie, for the kernels that load B operands straight
 // into registers.
 enum class RowsAt {
@@ -492,7 +498,7 @@ sl_status launch_direct(const LinearArgs &a, const GeluArg *ep, int32_t run_kind
 // (1 <= kw <= kSplitMaxWaves), whose waves split the item's windows, at most
 // split_windows_per_wave(n_win) each (1 or 2: the fewer that lets
 // kSplitMaxWaves waves cover the windows; 0: too many windows, over 32, for
-// this kernel). For few tokens; aligned or block-layout token rows.
+// this kernel). For few tokens; token rows in either layout, at any alignment.
 constexpr int kSplitSt = 1;
 constexpr int kSplitNt = 2;
 constexpr int kSplitWin = 2;
